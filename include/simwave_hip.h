@@ -238,6 +238,20 @@ typedef struct sw_fwd_io {
 
 sw_status sw_forward(sw_plan *plan, const sw_fwd_io *io, void *stream);
 
+/* Device bytes with which sw_forward_scratch / sw_forward_f64_scratch run
+ * faster than sw_forward / sw_forward_f64 (0: the plan has no use for any).
+ * Depends on the grid, the step count and the sources. */
+sw_status sw_plan_scratch(const sw_plan *plan, int64_t *bytes);
+
+/* sw_forward with `scratch_bytes` bytes of caller-owned device memory at
+ * `scratch`, which the call's launches write and read (two calls that may
+ * overlap need two).  With sw_plan_scratch's bytes, a 2D constant-density grid
+ * advances several steps per launch; results are bitwise those of sw_forward.
+ * With less, with NULL, with buffers not aligned to 16 bytes, with stencil_ms
+ * or for other plans the call is sw_forward. */
+sw_status sw_forward_scratch(sw_plan *plan, const sw_fwd_io *io, void *scratch, int64_t scratch_bytes,
+                             void *stream);
+
 /* ---- double precision (SW_F64 plans) ------------------------------------ */
 
 /* Model preparation of an SW_F64 plan: K = dt^2 c^2 in double precision from
@@ -266,6 +280,9 @@ typedef struct sw_fwd64_io {
  * double precision; the same steps and outputs as sw_forward (no checkpoints,
  * graphs, two-step sweeps or timing).  Enqueue only. */
 sw_status sw_forward_f64(sw_plan *plan, const sw_fwd64_io *io, void *stream);
+/* The same with scratch, as sw_forward_scratch. */
+sw_status sw_forward_f64_scratch(sw_plan *plan, const sw_fwd64_io *io, void *scratch, int64_t scratch_bytes,
+                                 void *stream);
 
 /* ---- adjoint and velocity gradient -------------------------------------- */
 

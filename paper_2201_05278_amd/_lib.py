@@ -100,8 +100,11 @@ SIGNATURES = {
                                  ctypes.POINTER(c_int64), ctypes.POINTER(c_int32), c_float_p]),
     "sw_model_prepare": (c_int32, [c_void_p, c_void_p, c_void_p, c_double, c_void_p, c_void_p]),
     "sw_forward": (c_int32, [c_void_p, ctypes.POINTER(FwdIO), c_void_p]),
+    "sw_plan_scratch": (c_int32, [c_void_p, ctypes.POINTER(c_int64)]),
+    "sw_forward_scratch": (c_int32, [c_void_p, ctypes.POINTER(FwdIO), c_void_p, c_int64, c_void_p]),
     "sw_model_prepare_f64": (c_int32, [c_void_p, c_void_p, c_double, c_void_p, c_void_p]),
     "sw_forward_f64": (c_int32, [c_void_p, ctypes.POINTER(Fwd64IO), c_void_p]),
+    "sw_forward_f64_scratch": (c_int32, [c_void_p, ctypes.POINTER(Fwd64IO), c_void_p, c_int64, c_void_p]),
     "sw_adjoint": (c_int32, [c_void_p, ctypes.POINTER(AdjIO), c_void_p]),
     "sw_plan_set_tiling": (c_int32, [c_void_p, ctypes.POINTER(Tiling)]),
     "sw_plan_get_tiling": (c_int32, [c_void_p, ctypes.POINTER(Tiling)]),

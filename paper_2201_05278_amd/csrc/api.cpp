@@ -11,6 +11,7 @@
 
 #include "runtime.h"
 #include "device64.h"
+#include "forward2d.h"
 
 namespace sw {
 const std::string &last_error();
@@ -746,8 +747,8 @@ sw_status sw_model_prepare(sw_plan *p, const float *vel, const float *rho, doubl
     return SW_OK;
 }
 
-// Enqueue the forward steps of io on s.
-static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, hipStream_t s)
+// Enqueue the forward steps of io on s; scratch: as in sw_forward_scratch.
+static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, void *scratch, int64_t scratch_bytes, hipStream_t s)
 {
     void *ws = io->workspace;
     StencilParams P;
@@ -786,8 +787,13 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, hipStream_t s)
     // span[k]: steps advanced by the launch bracketed by events 2k, 2k+1 (0: none)
     std::vector<int> span(size_t(io->nsteps_run), 0);
     const bool two = two_step_ready(p, io);
+    // 2D: the steps after `singly` run several to a launch
+    const Run2D<float> run{ws, io->wavelet, {io->field[0], io->field[1]}, io->traces, io->snaps, io->ckpt,
+                           io->saving_stride, io->ckpt_every, io->step0, io->nsteps_run};
+    const int singly = io->stencil_ms ? -1 : multi2d_singles<float>(p, run, scratch, scratch_bytes);
+    const int nloop = singly < 0 ? io->nsteps_run : singly;
     int k = 0;
-    while (k < io->nsteps_run) {
+    while (k < nloop) {
         const int n = io->step0 + k;
         float *cur = io->field[k % 2];
         float *nxt = io->field[(k + 1) % 2];
@@ -822,6 +828,7 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, hipStream_t s)
         SW_HIP(outputs(n, nxt));
         ++k;
     }
+    if (singly >= 0) return enqueue_multi2d<float>(p, run, singly, scratch, s);
     if (!ev.empty()) {
         const hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
@@ -839,7 +846,7 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, hipStream_t s)
     return SW_OK;
 }
 
-static sw_status forward_impl(sw_plan *p, const sw_fwd_io *io, void *stream)
+static sw_status forward_impl(sw_plan *p, const sw_fwd_io *io, void *scratch, int64_t scratch_bytes, void *stream)
 {
     if (!p || !io) return fail(SW_ERR_ARG, "NULL argument");
     if (p->prob.dtype == SW_F64) return fail(SW_ERR_STATE, "a double-precision plan runs by sw_forward_f64");
@@ -859,7 +866,7 @@ static sw_status forward_impl(sw_plan *p, const sw_fwd_io *io, void *stream)
          io->field2[0] == io->field[1] || io->field2[1] == io->field[0] || io->field2[1] == io->field[1]))
         return fail(SW_ERR_ARG, "field2 must be two more distinct wavefield buffers (or both NULL)");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!io->use_graph) return enqueue_forward(p, io, s);
+    if (!io->use_graph) return enqueue_forward(p, io, scratch, scratch_bytes, s);
 
     // Capture the whole loop once, on a private stream (the legacy default
     // stream cannot be captured), and replay the graph on the caller's stream
@@ -871,7 +878,8 @@ static sw_status forward_impl(sw_plan *p, const sw_fwd_io *io, void *stream)
         uint64_t(uintptr_t(io->traces)), uint64_t(uintptr_t(io->snaps)), uint64_t(io->saving_stride),
         uint64_t(uintptr_t(io->ckpt)), uint64_t(io->ckpt_every), uint64_t(io->step0),
         uint64_t(io->nsteps_run), p->generation, uint64_t(p->src.count), uint64_t(p->src.unode.size()),
-        uint64_t(p->rec.count), uint64_t(p->rec.node.size())};
+        uint64_t(p->rec.count), uint64_t(p->rec.node.size()), uint64_t(uintptr_t(scratch)),
+        uint64_t(scratch_bytes)};
     if (!p->graph_exec || p->graph_key != key) {
         if (p->graph_exec) {
             (void)hipGraphExecDestroy(static_cast<hipGraphExec_t>(p->graph_exec));
@@ -884,7 +892,7 @@ static sw_status forward_impl(sw_plan *p, const sw_fwd_io *io, void *stream)
         }
         hipStream_t cs = static_cast<hipStream_t>(p->capture_stream);
         SW_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        st = enqueue_forward(p, io, cs);
+        st = enqueue_forward(p, io, scratch, scratch_bytes, cs);
         hipGraph_t graph = nullptr;
         const hipError_t ec = hipStreamEndCapture(cs, &graph);
         if (st != SW_OK) {
@@ -903,11 +911,24 @@ static sw_status forward_impl(sw_plan *p, const sw_fwd_io *io, void *stream)
     return SW_OK;
 }
 
+sw_status sw_plan_scratch(const sw_plan *p, int64_t *bytes)
+{
+    set_error("");
+    if (!p || !bytes) return fail(SW_ERR_ARG, "NULL argument");
+    *bytes = multi2d_scratch_bytes(p);
+    return SW_OK;
+}
+
 sw_status sw_forward(sw_plan *p, const sw_fwd_io *io, void *stream)
+{
+    return sw_forward_scratch(p, io, nullptr, 0, stream);
+}
+
+sw_status sw_forward_scratch(sw_plan *p, const sw_fwd_io *io, void *scratch, int64_t scratch_bytes, void *stream)
 {
     Range range_("sw_forward");
     set_error("");
-    sw_status st = forward_impl(p, io, stream);
+    sw_status st = forward_impl(p, io, scratch, scratch_bytes, stream);
     if (st != SW_OK || !io->check_finite) return st;
     // optional check: non-finite trace samples of the steps run and final field values
     hipStream_t s = static_cast<hipStream_t>(stream);

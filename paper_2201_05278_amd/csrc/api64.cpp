@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device64.h"
+#include "forward2d.h"
 #include "runtime.h"
 
 using namespace sw;
@@ -121,6 +122,11 @@ sw_status sw_model_prepare_f64(sw_plan *p, const double *vel, double cmax, void 
 
 sw_status sw_forward_f64(sw_plan *p, const sw_fwd64_io *io, void *stream)
 {
+    return sw_forward_f64_scratch(p, io, nullptr, 0, stream);
+}
+
+sw_status sw_forward_f64_scratch(sw_plan *p, const sw_fwd64_io *io, void *scratch, int64_t scratch_bytes, void *stream)
+{
     Range range_("sw_forward_f64");
     set_error("");
     if (!p || !io) return fail(SW_ERR_ARG, "NULL argument");
@@ -146,7 +152,11 @@ sw_status sw_forward_f64(sw_plan *p, const sw_fwd64_io *io, void *stream)
         SW_HIP(launch_fill64(io->field[0], p->field_elems, s));
         SW_HIP(launch_fill64(io->field[1], p->field_elems, s));
     }
-    for (int k = 0; k < io->nsteps_run; ++k) {
+    // 2D: the steps after `singly` run several to a launch
+    const Run2D<double> run{ws, io->wavelet, {io->field[0], io->field[1]}, io->traces, io->snaps, nullptr,
+                            io->saving_stride, 0, io->step0, io->nsteps_run};
+    const int singly = multi2d_singles<double>(p, run, scratch, scratch_bytes);
+    for (int k = 0; k < (singly < 0 ? io->nsteps_run : singly); ++k) {
         const int n = io->step0 + k;
         double *cur = io->field[k % 2];
         double *nxt = io->field[(k + 1) % 2];
@@ -160,7 +170,7 @@ sw_status sw_forward_f64(sw_plan *p, const sw_fwd64_io *io, void *stream)
             SW_HIP(launch_snapshot64(g, nxt, io->snaps + size_t((n + 1) / io->saving_stride - 1) * p->grid_nodes,
                                      s));
     }
-    return SW_OK;
+    return singly < 0 ? SW_OK : enqueue_multi2d<double>(p, run, singly, scratch, s);
 }
 
 }  // extern "C"

@@ -271,8 +271,10 @@ class Propagator:
         io.saving_stride = int(saving_stride)
         io.step0 = int(step0)
         io.nsteps_run = nrun
-        self._keep = (wavelet, fields, traces, snaps)
-        L.check("sw_forward_f64", L.lib().sw_forward_f64(self._plan, ctypes.byref(io), _stream()))
+        scratch = self._scratch(False)
+        self._keep = (wavelet, fields, traces, snaps, scratch)
+        L.check("sw_forward_f64", L.lib().sw_forward_f64_scratch(
+            self._plan, ctypes.byref(io), _ptr(scratch), scratch.numel() if scratch is not None else 0, _stream()))
         return ForwardResult(traces, fields, nrun % 2, snaps, None, 0)
 
     # ---- tiling -------------------------------------------------------------
@@ -321,6 +323,25 @@ class Propagator:
         if getattr(self, "_field2", None) is None:
             self._field2 = (self.new_field(), self.new_field())
         return self._field2
+
+    def _scratch(self, use_graph):
+        """Device scratch of a forward, or None.  One per call, so that runs of one
+        plan may overlap on several streams; a graph keeps its own, since it is
+        replayed only on the buffers it was captured with."""
+        n = ctypes.c_int64(0)
+        L.check("sw_plan_scratch", L.lib().sw_plan_scratch(self._plan, ctypes.byref(n)))
+        if n.value == 0:
+            return None
+        kept = getattr(self, "_graph_scratch", None) if use_graph else None
+        if kept is None or kept.numel() != n.value:
+            try:
+                kept = torch.empty(n.value, dtype=torch.uint8, device=self.device)
+            except torch.cuda.OutOfMemoryError:
+                return None                     # the single-step kernels need none
+        if use_graph:
+            kept.record_stream(torch.cuda.current_stream(self.device))
+            self._graph_scratch = kept
+        return kept
 
     def _fwd_io(self, wavelet, fields, traces):
         lay = self.layout
@@ -384,8 +405,10 @@ class Propagator:
         spare = self._spare_fields()
         if spare is not None:
             io.field2[0], io.field2[1] = spare[0].data_ptr(), spare[1].data_ptr()
-        self._keep = (wavelet, fields, traces, snaps, ckpt)
-        L.check("sw_forward", L.lib().sw_forward(self._plan, ctypes.byref(io), _stream()))
+        scratch = self._scratch(use_graph)
+        self._keep = (wavelet, fields, traces, snaps, ckpt, scratch)
+        L.check("sw_forward", L.lib().sw_forward_scratch(
+            self._plan, ctypes.byref(io), _ptr(scratch), scratch.numel() if scratch is not None else 0, _stream()))
         return ForwardResult(traces, fields, nrun % 2, snaps, ckpt, int(checkpoint_every))
 
     def adjoint(self, wavelet, residual, ckpt, checkpoint_every, want_src_adjoint=False):

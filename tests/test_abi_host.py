@@ -385,3 +385,25 @@ def test_roctx_ranges_open_the_tracing_library():
         before_after, st = out.stdout.split()[:2], int(out.stdout.split()[2])
         assert " ".join(before_after) == want, out.stdout
         assert L.STATUS[st] == "SW_ERR_ARG"
+
+
+def test_scratch_is_asked_for_by_2d_constant_density_only():
+    import ctypes
+    lib = L.lib()
+
+    def scratch(n, so, **kw):
+        prop = Propagator(n, (10.0,) * len(n), so, 1e-4, 50, nbl=8, **kw)
+        b = ctypes.c_int64(-1)
+        assert lib.sw_plan_scratch(prop._plan, ctypes.byref(b)) == 0
+        return b.value, prop.layout.field_elems
+
+    for so in (2, 8, 20):
+        got, elems = scratch((60, 80), so)
+        assert got >= 2 * 4 * elems               # the second pair of levels at least
+    got, elems = scratch((60, 80), 8, dtype="float64")
+    assert got >= 2 * 8 * elems
+    assert scratch((60, 80), 16, dtype="float64")[0] == 0       # no tile is left beside its halo
+    assert scratch((1200, 2000), 20)[0] == 0      # single steps are faster there
+    assert scratch((40, 40, 40), 8)[0] == 0
+    assert scratch((60, 80), 8, scheme="vd_staggered")[0] == 0
+    assert lib.sw_plan_scratch(None, None) != 0
