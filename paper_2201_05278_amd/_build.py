@@ -12,7 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsimwave_hip.so")
 SOURCES = ["plan.cpp", "api.cpp", "api64.cpp", "batch.cpp", "trace.cpp", "k_dispatch.cpp", "forward2d.cpp", "k_points.hip", "k_adjoint_vd.hip",
-           "k_f64.hip", "k_multi2d.hip"] + \
+           "k_f64.hip", "k_multi2d.hip", "vec.cpp", "k_vec1.hip", "k_vec2.hip", "k_vec3.hip",
+           "k_vec64.hip"] + \
           [f"k_r{r}.hip" for r in range(1, 11)]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

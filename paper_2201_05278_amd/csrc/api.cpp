@@ -270,6 +270,12 @@ Tiling choose_tiling(const sw_plan *p)
     return t;
 }
 
+// No choice of the caller's or of the autotuner's: the library picks.
+bool default_tiling(const sw_plan *p)
+{
+    return !p->tile_tx && !p->tile_zc && p->tile_nt < 0 && !p->tile_pf && p->tile_ts != 2 && p->tile_occ < 0 && !p->tile_order;
+}
+
 void fill_params(const sw_plan *p, void *ws, StencilParams &P)
 {
     std::memset(&P, 0, sizeof(P));
@@ -312,8 +318,9 @@ void set_tiles(const sw_plan *p, const Tiling &t, StencilParams &P)
     P.nzc = (p->dims[0] + P.zc - 1) / P.zc;
 }
 
-hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, hipStream_t s)
+hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, const VecChoice &vec, hipStream_t s)
 {
+    if (vec.tile >= 0) return launch_vec<float>(p->r, vec, mode, P, s);
     Tiling t = choose_tiling(p);
     t.ts = 1;
     // the staggered imaging stencil holds two more values per node than the
@@ -787,6 +794,7 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, void *scratch,
     // span[k]: steps advanced by the launch bracketed by events 2k, 2k+1 (0: none)
     std::vector<int> span(size_t(io->nsteps_run), 0);
     const bool two = two_step_ready(p, io);
+    const VecChoice vec = choose_vec(p, MODE_FWD);
     // 2D: the steps after `singly` run several to a launch
     const Run2D<float> run{ws, io->wavelet, {io->field[0], io->field[1]}, io->traces, io->snaps, io->ckpt,
                            io->saving_stride, io->ckpt_every, io->step0, io->nsteps_run};
@@ -817,11 +825,12 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, void *scratch,
             continue;
         }
         SW_HIP(checkpoint(n, cur, nxt));
-        if (p->mirror) SW_HIP(launch_ghost_fill(g, p->bcm, p->ghost, cur, s));
+        // the vector tiles make mirror ghosts themselves (checkpoints keep those of the fill)
+        if (p->mirror && (vec.tile < 0 || io->ckpt)) SW_HIP(launch_ghost_fill(g, p->bcm, p->ghost, cur, s));
         P.cur = cur;
         P.nxt = nxt;
         if (!ev.empty()) SW_HIP(hipEventRecord(ev[2 * k], s));
-        SW_HIP(stencil(p, MODE_FWD, P, s));
+        SW_HIP(stencil(p, MODE_FWD, P, vec, s));
         if (!ev.empty()) SW_HIP(hipEventRecord(ev[2 * k + 1], s));
         span[k] = 1;
         if (src.count) SW_HIP(launch_inject(src, nxt, nullptr, io->wavelet + size_t(n) * src.count, s));
@@ -992,6 +1001,8 @@ sw_status sw_adjoint(sw_plan *p, const sw_adj_io *io, void *stream)
     float *acur = io->adj[0];   // phi^{m+1}
     float *anxt = io->adj[1];   // phi^{m+2}, overwritten by phi^m
     const int nseg = (N + E - 1) / E;
+    const VecChoice vfwd = choose_vec(p, MODE_FWD), vstore = choose_vec(p, MODE_STORE), vimage = choose_vec(p, MODE_IMAGE),
+                    vimage2 = choose_vec(p, MODE_IMAGE2);
     const Geom gm = make_geom(p);
     // staggered face term, formed two steps at a time: the term of step m
     // (phi^{m+1} against u^m) is deferred to the start of step m - 1, where
@@ -1019,7 +1030,7 @@ sw_status sw_adjoint(sw_plan *p, const sw_adj_io *io, void *stream)
             P.store = lvl;
             P.grad = nullptr;
             P.ustore = vd ? io->segment + size_t(E + i) * fe : nullptr;
-            SW_HIP(stencil(p, MODE_STORE, P, s));
+            SW_HIP(stencil(p, MODE_STORE, P, vstore, s));
             if (src.count)
                 SW_HIP(launch_inject(src, nxt, vd ? nullptr : lvl, io->wavelet + size_t(n) * src.count, s));
         }
@@ -1050,24 +1061,24 @@ sw_status sw_adjoint(sw_plan *p, const sw_adj_io *io, void *stream)
                     P.store = io->segment + size_t(m - k) * fe;
                     P.store2 = io->segment + size_t(m + 1 - k) * fe;
                     P.grad = io->grad_m;
-                    SW_HIP(stencil(p, MODE_IMAGE2, P, s));
+                    SW_HIP(stencil(p, MODE_IMAGE2, P, vimage2, s));
                     gpend = -1;
                 } else if (pair_image && m > k) {
                     // deferred to step m - 1 of this segment (the gradient is then
                     // read and written once per two steps)
                     P.store = nullptr;
                     P.grad = nullptr;
-                    SW_HIP(stencil(p, MODE_FWD, P, s));
+                    SW_HIP(stencil(p, MODE_FWD, P, vfwd, s));
                     gpend = m;
                 } else {
                     P.store = io->segment + size_t(m - k) * fe;
                     P.grad = io->grad_m;
-                    SW_HIP(stencil(p, MODE_IMAGE, P, s));
+                    SW_HIP(stencil(p, MODE_IMAGE, P, vimage, s));
                 }
             } else {
                 P.store = nullptr;
                 P.grad = nullptr;
-                SW_HIP(stencil(p, MODE_FWD, P, s));
+                SW_HIP(stencil(p, MODE_FWD, P, vfwd, s));
             }
             if (m >= 1) {
                 if (rec.count) SW_HIP(launch_inject(rec, anxt, nullptr, io->residual + size_t(m - 1) * rec.count, s));

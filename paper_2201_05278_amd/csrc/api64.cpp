@@ -145,6 +145,7 @@ sw_status sw_forward_f64_scratch(sw_plan *p, const sw_fwd64_io *io, void *scratc
     StencilParamsT<double> P;
     fill_params64(p, ws, P);
     const Tiling t = choose_tiling(p);
+    const VecChoice vec = choose_vec(p, MODE_FWD);
     const PointTable64 src = table64(p->src, p->ws.src, ws);
     const PointTable64 rec = table64(p->rec, p->ws.rec, ws);
     const Geom g = make_geom(p);
@@ -160,10 +161,11 @@ sw_status sw_forward_f64_scratch(sw_plan *p, const sw_fwd64_io *io, void *scratc
         const int n = io->step0 + k;
         double *cur = io->field[k % 2];
         double *nxt = io->field[(k + 1) % 2];
-        if (p->mirror) SW_HIP(launch_ghost64(g, p->bcm, p->ghost, cur, s));
+        if (p->mirror && vec.tile < 0) SW_HIP(launch_ghost64(g, p->bcm, p->ghost, cur, s));
         P.cur = cur;
         P.nxt = nxt;
-        SW_HIP(launch_const64(p->r, p->ndim, t.tx, t.nw, P, s));
+        if (vec.tile >= 0) SW_HIP(launch_vec<double>(p->r, vec, MODE_FWD, P, s));
+        else SW_HIP(launch_const64(p->r, p->ndim, t.tx, t.nw, P, s));
         if (src.count) SW_HIP(launch_inject64(src, nxt, io->wavelet + size_t(n) * src.count, s));
         if (rec.count) SW_HIP(launch_record64(rec, nxt, io->traces + size_t(n) * rec.count, s));
         if (io->snaps && io->saving_stride > 0 && (n + 1) % io->saving_stride == 0)

@@ -123,8 +123,11 @@ sw_status batch_step(sw_batch *b, void *table, int k, bool points, hipStream_t s
     const auto *params = reinterpret_cast<const StencilParams *>(t + b->off_params);
     const auto *tiles = reinterpret_cast<const int *>(t + b->off_tiles);
     const auto *pts = reinterpret_cast<const ShotPoints *>(t + b->off_points);
-    SW_HIP(launch_const_batch(b->r, b->ndim, b->tiling, params, tiles, b->nshots, k % 2,
-                              persistent_blocks(b), s));
+    const Tiling &bt = b->tiling;
+    if (b->ndim == 3 && bt.tx == 16 && bt.nw == 4 && bt.nt == 1 && bt.pf == 1)
+        SW_HIP(launch_vec_batch(b->r, params, tiles, b->nshots, k % 2, persistent_blocks(b), s));
+    else
+        SW_HIP(launch_const_batch(b->r, b->ndim, bt, params, tiles, b->nshots, k % 2, persistent_blocks(b), s));
     if (points) {
         SW_HIP(launch_inject_batch(pts, b->nshots, b->max_uniq, b->max_per_node, k, k % 2, s));
         SW_HIP(launch_record_batch(pts, b->nshots, b->max_rec, b->max_per_point, k, k % 2, s));
@@ -436,45 +439,52 @@ sw_status sw_plan_autotune(sw_plan *p, const sw_fwd_io *io, const char *cache_pa
     hipEvent_t e0, e1;
     SW_HIP(hipEventCreate(&e0));
     SW_HIP(hipEventCreate(&e1));
-    float best = std::numeric_limits<float>::max();
-    sw_tiling best_t{0, 0, 0, -1, 0, 0, 0, -1, 0};
-    StencilParams P;
-    fill_params(p, io->workspace, P);
-    P.cur = io->field[0];
-    P.nxt = io->field[1];
+    // candidates: the library's own choice (vector tiles, 3D constant density),
+    // then every shape, chunk, cache policy, prefetch depth, cap and order
+    const sw_tiling own{0, 0, 0, -1, 0, 0, 0, -1, 0};
+    std::vector<sw_tiling> cands;
+    if (const3 && p->ndim == 3) cands.push_back(own);
     for (auto sh : shapes)
         for (int zc : zc_candidates(p->dims[0], p->r))
             for (int nt : {0, 1})
                 for (int pf : {1, 2})
                     for (int occ : {-1, 4})
                         for (int order : {1, 2}) {
-                // a cap of 4 blocks per CU is tried for single-step 4-wave block tiles
-                if (occ == 4 && (!const3 || sh.wt || sh.ts == 2 || sh.nw != 4 || p->ndim != 3)) continue;
-                if ((!const3 || sh.wt || sh.ts == 2) && pf == 2) continue;
-                // the block order applies to single-step block tiles in 3D
-                if (order == 2 && (sh.wt || sh.ts == 2 || p->ndim != 3)) continue;
-                const sw_tiling cand{sh.tx, sh.nw, zc, nt, pf, sh.wt, sh.ts, occ, order};
-                st = sw_plan_set_tiling(p, &cand);
-                if (st != SW_OK) continue;
-                // per-step time: single sweeps, or two-step sweeps over half as many launches
-                auto run = [&]() -> hipError_t {
-                    if (sh.ts == 2)
-                        return stencil_two(p, io, 0, io->field[0], io->field[1], io->field2[0], io->field2[1],
-                                           false, s);
-                    return stencil(p, MODE_FWD, P, s);
-                };
-                for (int w = 0; w < 2; ++w) SW_HIP(run());
-                SW_HIP(hipEventRecord(e0, s));
-                const int reps = 10;
-                for (int k = 0; k < reps; ++k) SW_HIP(run());
-                SW_HIP(hipEventRecord(e1, s));
-                SW_HIP(hipEventSynchronize(e1));
-                const float ms = elapsed(e0, e1) / reps / sh.ts;
-                if (ms < best) {
-                    best = ms;
-                    best_t = cand;
-                }
-            }
+                            // a cap of 4 blocks per CU is tried for single-step 4-wave block tiles
+                            if (occ == 4 && (!const3 || sh.wt || sh.ts == 2 || sh.nw != 4 || p->ndim != 3)) continue;
+                            if ((!const3 || sh.wt || sh.ts == 2) && pf == 2) continue;
+                            // the block order applies to single-step block tiles in 3D
+                            if (order == 2 && (sh.wt || sh.ts == 2 || p->ndim != 3)) continue;
+                            cands.push_back({sh.tx, sh.nw, zc, nt, pf, sh.wt, sh.ts, occ, order});
+                        }
+    float best = std::numeric_limits<float>::max();
+    sw_tiling best_t = own;
+    StencilParams P;
+    fill_params(p, io->workspace, P);
+    P.cur = io->field[0];
+    P.nxt = io->field[1];
+    for (const sw_tiling &cand : cands) {
+        st = sw_plan_set_tiling(p, &cand);
+        if (st != SW_OK) continue;
+        const VecChoice vec = choose_vec(p, MODE_FWD);
+        // per-step time: single sweeps, or two-step sweeps over half as many launches
+        auto run = [&]() -> hipError_t {
+            if (cand.ts == 2)
+                return stencil_two(p, io, 0, io->field[0], io->field[1], io->field2[0], io->field2[1], false, s);
+            return stencil(p, MODE_FWD, P, vec, s);
+        };
+        for (int w = 0; w < 2; ++w) SW_HIP(run());
+        SW_HIP(hipEventRecord(e0, s));
+        const int reps = 10;
+        for (int k = 0; k < reps; ++k) SW_HIP(run());
+        SW_HIP(hipEventRecord(e1, s));
+        SW_HIP(hipEventSynchronize(e1));
+        const float ms = elapsed(e0, e1) / reps / std::max(1, cand.ts);
+        if (ms < best) {
+            best = ms;
+            best_t = cand;
+        }
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     st = sw_plan_set_tiling(p, &best_t);

@@ -7,6 +7,7 @@
 
 #include "device.h"
 #include "plan.h"
+#include "vec.h"
 
 #define SW_HIP(call)                                                                          \
     do {                                                                                      \
@@ -30,9 +31,11 @@ bool vd_shape_ok(int tx, int nw);
 bool wave_shape_ok(int tx, int nw);
 int default_zc(const sw_plan *p, int tx, int64_t want, int ts = 1);
 Tiling choose_tiling(const sw_plan *p);
+bool default_tiling(const sw_plan *p);
 void fill_params(const sw_plan *p, void *ws, StencilParams &P);
 void set_tiles(const sw_plan *p, const Tiling &t, StencilParams &P);
-hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, hipStream_t s);
+// One stencil launch; vec: choose_vec's answer for the mode, asked once per run.
+hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, const VecChoice &vec, hipStream_t s);
 bool tb_shape_ok(int r, int tx, int nw);
 bool two_step_ready(const sw_plan *p, const sw_fwd_io *io);
 // One two-step sweep from (cur = p^n, prv = p^{n-1}) to out1 = p^{n+1},

@@ -1,0 +1,48 @@
+// Vector tiles of the 3D constant-density stencil (stencil_vec.h): tiles,
+// launchers and the choice of tile and z chunk.
+#pragma once
+
+#include "device.h"
+
+struct sw_plan;
+
+namespace sw {
+
+// TX rows x lpr 16-byte vectors of columns, one thread per vector.
+struct VecTile {
+    int tx, lpr;
+};
+template <typename T> inline constexpr VecTile kVecTiles[8] = {{8, 16}, {12, 16}, {16, 16}, {24, 16},
+                                                        {8, 32}, {12, 32}, {16, 32}, {24, 32}};
+// doubles: the same columns with twice the threads per row
+template <> inline constexpr VecTile kVecTiles<double>[8] = {{4, 32}, {8, 32}, {12, 32}, {16, 32},
+                                                      {24, 32}, {4, 64}, {8, 64}, {12, 64}};
+constexpr int kVecTileCount = 8;
+
+constexpr int kVecMirror = 8;   // MODE_FWD of a plan with mirror sides: kernels of their own
+
+struct VecChoice {
+    int tile = -1, zc = 0;      // tile -1: the scalar tiles
+    bool mirror = false;        // the plan has mirror sides
+};
+
+// Tile and chunk of a 3D constant-density plan with default tiling in a mode.
+VecChoice choose_vec(const sw_plan *p, int mode);
+
+// Launch with a choice: sets the tile counts of P.
+template <typename T>
+hipError_t launch_vec(int r, const VecChoice &c, int mode, StencilParamsT<T> &P, hipStream_t s);
+
+template <typename T, int R>
+hipError_t launch_vec_radius(int tile, int mode, StencilParamsT<T> &P, hipStream_t s);
+template <typename T, int R>
+int vec_resident_radius(int tile, int mode);
+
+// The batch launch on 16-row, 64-column vector tiles (arguments as launch_const_batch).
+hipError_t launch_vec_batch(int r, const StencilParams *shots, const int *tile_start, int nshots, int parity, int nblocks,
+                            hipStream_t s);
+template <int R>
+hipError_t launch_vec_batch_radius(const StencilParams *shots, const int *tile_start, int nshots, int parity, int nblocks,
+                                   hipStream_t s);
+
+}  // namespace sw
