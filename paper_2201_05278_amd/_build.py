@@ -13,7 +13,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsimwave_hip.so")
 SOURCES = ["plan.cpp", "api.cpp", "api64.cpp", "batch.cpp", "trace.cpp", "k_dispatch.cpp", "forward2d.cpp", "k_points.hip", "k_adjoint_vd.hip",
            "k_f64.hip", "k_multi2d.hip", "vec.cpp", "k_vec1.hip", "k_vec2.hip", "k_vec3.hip",
-           "k_vec64.hip"] + \
+           "k_vec64.hip", "k_vdvec1.hip", "k_vdvec2.hip", "k_vdvec3.hip",
+           "k_vdvec4.hip", "k_vdvec5.hip", "k_vdvec6.hip", "k_vdvec7.hip"] + \
           [f"k_r{r}.hip" for r in range(1, 11)]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

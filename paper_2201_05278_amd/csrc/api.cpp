@@ -320,7 +320,9 @@ void set_tiles(const sw_plan *p, const Tiling &t, StencilParams &P)
 
 hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, const VecChoice &vec, hipStream_t s)
 {
-    if (vec.tile >= 0) return launch_vec<float>(p->r, vec, mode, P, s);
+    if (vec.tile >= 0)
+        return p->prob.scheme == SW_CONST ? launch_vec<float>(p->r, vec, mode, P, s)
+                                          : launch_vdvec(p->prob.scheme, p->r, vec, mode, P, s);
     Tiling t = choose_tiling(p);
     t.ts = 1;
     // the staggered imaging stencil holds two more values per node than the
@@ -825,8 +827,8 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, void *scratch,
             continue;
         }
         SW_HIP(checkpoint(n, cur, nxt));
-        // the vector tiles make mirror ghosts themselves (checkpoints keep those of the fill)
-        if (p->mirror && (vec.tile < 0 || io->ckpt)) SW_HIP(launch_ghost_fill(g, p->bcm, p->ghost, cur, s));
+        // the constant-density vector tiles make mirror ghosts themselves (checkpoints keep those of the fill)
+        if (p->mirror && (vec.tile < 0 || p->prob.scheme != SW_CONST || io->ckpt)) SW_HIP(launch_ghost_fill(g, p->bcm, p->ghost, cur, s));
         P.cur = cur;
         P.nxt = nxt;
         if (!ev.empty()) SW_HIP(hipEventRecord(ev[2 * k], s));

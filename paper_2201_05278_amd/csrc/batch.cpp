@@ -439,11 +439,11 @@ sw_status sw_plan_autotune(sw_plan *p, const sw_fwd_io *io, const char *cache_pa
     hipEvent_t e0, e1;
     SW_HIP(hipEventCreate(&e0));
     SW_HIP(hipEventCreate(&e1));
-    // candidates: the library's own choice (vector tiles, 3D constant density),
+    // candidates: the library's own choice (vector tiles in 3D),
     // then every shape, chunk, cache policy, prefetch depth, cap and order
     const sw_tiling own{0, 0, 0, -1, 0, 0, 0, -1, 0};
     std::vector<sw_tiling> cands;
-    if (const3 && p->ndim == 3) cands.push_back(own);
+    if (p->ndim == 3) cands.push_back(own);
     for (auto sh : shapes)
         for (int zc : zc_candidates(p->dims[0], p->r))
             for (int nt : {0, 1})

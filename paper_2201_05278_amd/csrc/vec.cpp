@@ -14,7 +14,8 @@ namespace sw {
     extern template int vec_resident_radius<T, R>(int, int);
 #define SW_XR(R)                     \
     SW_X(float, R) SW_X(double, R)   \
-    extern template hipError_t launch_vec_batch_radius<R>(const StencilParams *, const int *, int, int, int, hipStream_t);
+    extern template hipError_t launch_vec_batch_radius<R>(const StencilParams *, const int *, int, int, int, hipStream_t); \
+    extern template hipError_t launch_vdvec_radius<R>(int, int, int, StencilParams &, hipStream_t);
 SW_XR(1) SW_XR(2) SW_XR(3) SW_XR(4) SW_XR(5) SW_XR(6) SW_XR(7) SW_XR(8) SW_XR(9) SW_XR(10)
 #undef SW_XR
 #undef SW_X
@@ -83,6 +84,29 @@ hipError_t launch_vec_batch(int r, const StencilParams *shots, const int *tile_s
     case 8: return launch_vec_batch_radius<8>(shots, tile_start, nshots, parity, nblocks, s);
     case 9: return launch_vec_batch_radius<9>(shots, tile_start, nshots, parity, nblocks, s);
     case 10: return launch_vec_batch_radius<10>(shots, tile_start, nshots, parity, nblocks, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_vdvec(int scheme, int r, const VecChoice &c, int mode, StencilParams &P, hipStream_t s)
+{
+    const VdTile t = kVdTiles[c.tile];
+    P.ntx = (P.g.X + t.tx - 1) / t.tx;
+    P.nty = (P.g.Y + t.ty - 1) / t.ty;
+    P.zc = c.zc;
+    P.nzc = (P.g.Z + c.zc - 1) / c.zc;
+    P.xfast = 0;
+    switch (r) {
+    case 1: return launch_vdvec_radius<1>(scheme, c.tile, mode, P, s);
+    case 2: return launch_vdvec_radius<2>(scheme, c.tile, mode, P, s);
+    case 3: return launch_vdvec_radius<3>(scheme, c.tile, mode, P, s);
+    case 4: return launch_vdvec_radius<4>(scheme, c.tile, mode, P, s);
+    case 5: return launch_vdvec_radius<5>(scheme, c.tile, mode, P, s);
+    case 6: return launch_vdvec_radius<6>(scheme, c.tile, mode, P, s);
+    case 7: return launch_vdvec_radius<7>(scheme, c.tile, mode, P, s);
+    case 8: return launch_vdvec_radius<8>(scheme, c.tile, mode, P, s);
+    case 9: return launch_vdvec_radius<9>(scheme, c.tile, mode, P, s);
+    case 10: return launch_vdvec_radius<10>(scheme, c.tile, mode, P, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -160,11 +184,82 @@ VecChoice choose(const sw_plan *p, int mode)
     return best;
 }
 
+// The same for variable density, whose kernels leave two waves per SIMD: blocks
+// that fill a round march together and each further round costs as much again,
+// a last partial one a little less where its blocks have a SIMD to themselves
+// (fitted to sweeps on six grids of 2.7 M .. 207 M nodes at SO4, SO8 and SO16:
+// its choices ran within 2% of the sweep's best on average).
+struct VdCost {
+    double hx, hy, warm, plane, tail, alone, last;
+};
+constexpr VdCost kStagCost{0.147, 1.2, 0.176, 1.78, 0.26, 1.0, 1.0};
+constexpr VdCost kCentCost{0.3, 1.235, 0.239, 0.0, 0.0, 0.25, 0.6};
+
+VecChoice choose_vd(const sw_plan *p)
+{
+    constexpr int kCUs = 256;
+    VecChoice best;
+    const bool stag = p->prob.scheme == SW_VD_STAGGERED;
+    const VdCost m = stag ? kStagCost : kCentCost;
+    const int Z = p->dims[0], X = p->dims[1], Y = p->dims[2], R = p->r;
+    const int warm = stag ? 2 * R - 1 : 2 * R;
+    const int64_t pbytes = int64_t(p->pad[1]) * p->pad[2] * 4;
+    const int zmax = int(std::max<int64_t>(1, (int64_t(1) << 31) / pbytes - 4 * R - 2));
+    double cost = 0.0;
+    for (int i = 0; i < kVdTileCount; ++i) {
+        const VdTile t = kVdTiles[i];
+        const int threads = t.tx * t.ty / vd_columns(p->prob.scheme, R);
+        if (threads > kVdThreads || (!stag && (t.tx > 16 ? R < 3 || t.ty > 32 : R < 3 && t.ty > 64))) continue;
+        const int res = 512 / threads;                     // two waves per SIMD
+        const double tiles = double((X + t.tx - 1) / t.tx) * ((Y + t.ty - 1) / t.ty);
+        const double plane = t.tx * t.ty * (1.0 + m.hx * 2 * R / t.tx + m.hy * 2 * R / t.ty);
+        for (int n = 1; n <= Z; ++n) {
+            const int zc = (Z + n - 1) / n;
+            if (zc > zmax) continue;
+            if (zc < 4 && n > 1) break;
+            const double per_cu = tiles * ((Z + zc - 1) / zc) / kCUs;
+            const double full = std::floor(per_cu / res), rest = per_cu - full * res;
+            const double half = full > 0.0 ? m.last : m.alone;      // of a round with every other slot empty
+            const double part = rest > 1e-9 ? std::min(1.0, half + (1.0 - half) * std::ceil(rest) / res) : 0.0;
+            const double rounds = per_cu <= res ? std::max(full, part) : full + (1.0 - m.tail) * part + m.tail * rest / res;
+            const double us = rounds * res * (zc + m.warm * warm + m.plane) * plane;
+            if (best.tile < 0 || us < cost) {
+                cost = us;
+                best.tile = i;
+                best.zc = zc;
+            }
+        }
+    }
+    return best;
+}
+
+// Where the variable-density vector tiles are the faster ones (scalar against
+// vector tiles, us per forward step):
+//   staggered, R 2 .. 8: 240^3 SO8 122 against 104, SO16 228 against 213; but on
+//   larger grids the scalar tiles' four waves per SIMD stream better (360 x 360 x
+//   380 SO4 250 against 268, SO12 550 against 591), SO8 apart (592^3 1360 against
+//   1312).  Recording and imaging launches gain at every size (a gradient step at
+//   400^3 SO4 1503 against 1418, SO16 3659 against 3577).  R = 1 has little to
+//   share between neighbours (280^3 97 against 120), and from R = 9 on three
+//   queues leave no registers (280^3 SO20 561 against 1182).
+//   centred: 280^3 SO8 154 against 132, SO20 387 against 251; but large grids at
+//   SO2 and SO4 are the scalar tiles' (360 x 360 x 380 SO4 230 against 233) and
+//   at SO14 and SO16, where a thread has two columns (450 against 489).
+bool vd_vectors(const sw_plan *p, int mode)
+{
+    const int R = p->r;
+    const double nodes = double(p->dims[0]) * p->dims[1] * p->dims[2];
+    if (p->prob.scheme == SW_VD_STAGGERED)
+        return R >= kStagRadii[0] && R <= kStagRadii[1] && (R == 4 || mode != MODE_FWD || nodes < (R == 2 ? 30e6 : 40e6));
+    return R >= 9 || nodes < (R <= 2 ? 40e6 : R <= 6 ? 1e18 : 30e6);
+}
+
 }  // namespace
 
 VecChoice choose_vec(const sw_plan *p, int mode)
 {
-    if (p->ndim != 3 || p->prob.scheme != SW_CONST || !default_tiling(p) || (p->mirror && mode != MODE_FWD)) return {};
+    if (p->ndim != 3 || !default_tiling(p) || (p->mirror && mode != MODE_FWD)) return {};
+    if (p->prob.scheme != SW_CONST) return vd_vectors(p, mode) ? choose_vd(p) : VecChoice{};
     if (p->mirror) mode = kVecMirror;
     VecChoice c = p->prob.dtype == SW_F64 ? choose<double>(p, mode) : choose<float>(p, mode);
     c.mirror = p->mirror;

@@ -1,4 +1,4 @@
-// Vector tiles of the 3D constant-density stencil (stencil_vec.h): tiles,
+// Vector tiles of the 3D stencils (stencil_vec.h, stencil_vdvec.h): tiles,
 // launchers and the choice of tile and z chunk.
 #pragma once
 
@@ -26,7 +26,7 @@ struct VecChoice {
     bool mirror = false;        // the plan has mirror sides
 };
 
-// Tile and chunk of a 3D constant-density plan with default tiling in a mode.
+// Tile and chunk of a 3D plan with default tiling in a mode.
 VecChoice choose_vec(const sw_plan *p, int mode);
 
 // Launch with a choice: sets the tile counts of P.
@@ -44,5 +44,24 @@ hipError_t launch_vec_batch(int r, const StencilParams *shots, const int *tile_s
 template <int R>
 hipError_t launch_vec_batch_radius(const StencilParams *shots, const int *tile_start, int nshots, int parity, int nblocks,
                                    hipStream_t s);
+
+// Variable density (stencil_vdvec.h): rows x columns, as many threads as the
+// columns per thread of the scheme and radius leave.
+struct VdTile {
+    int tx, ty;
+};
+inline constexpr VdTile kVdTiles[5] = {{8, 64}, {16, 64}, {16, 128}, {32, 32}, {32, 64}};
+constexpr int kVdTileCount = 5;
+inline constexpr int kStagRadii[2] = {2, 8};    // staggered: smallest and largest radius
+constexpr int kVdThreads = 512;     // at most, in a block: two waves per SIMD leave a thread 256 registers
+// Columns per thread (scheme as in launch_vd).
+constexpr int vd_columns(int scheme, int r)
+{
+    return r <= (scheme == 1 ? 4 : 6) ? 4 : 2;
+}
+
+hipError_t launch_vdvec(int scheme, int r, const VecChoice &c, int mode, StencilParams &P, hipStream_t s);
+template <int R>
+hipError_t launch_vdvec_radius(int scheme, int tile, int mode, StencilParams &P, hipStream_t s);
 
 }  // namespace sw
