@@ -785,10 +785,10 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, void *scratch,
         if (e == hipSuccess) e = launch_copy(slot + p->field_elems, prv, p->field_elems, s);
         return e;
     };
-    // receivers and snapshot of step n, whose new level p^{n+1} is in f
-    auto outputs = [&](int n, const float *f) -> hipError_t {
+    // receivers (record) and snapshot of step n, whose new level p^{n+1} is in f
+    auto outputs = [&](int n, const float *f, bool record = true) -> hipError_t {
         hipError_t e = hipSuccess;
-        if (rec.count) e = launch_record(rec, f, io->traces + size_t(n) * rec.count, s);
+        if (rec.count && record) e = launch_record(rec, f, io->traces + size_t(n) * rec.count, s);
         if (e == hipSuccess && io->snaps && io->saving_stride > 0 && (n + 1) % io->saving_stride == 0)
             e = launch_snapshot(g, f, io->snaps + size_t((n + 1) / io->saving_stride - 1) * p->grid_nodes, s);
         return e;
@@ -803,6 +803,7 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, void *scratch,
     const int singly = io->stencil_ms ? -1 : multi2d_singles<float>(p, run, scratch, scratch_bytes);
     const int nloop = singly < 0 ? io->nsteps_run : singly;
     int k = 0;
+    bool owed = false;                   // the level in cur is not recorded yet
     while (k < nloop) {
         const int n = io->step0 + k;
         float *cur = io->field[k % 2];
@@ -835,9 +836,16 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, void *scratch,
         SW_HIP(stencil(p, MODE_FWD, P, vec, s));
         if (!ev.empty()) SW_HIP(hipEventRecord(ev[2 * k + 1], s));
         span[k] = 1;
-        if (src.count) SW_HIP(launch_inject(src, nxt, nullptr, io->wavelet + size_t(n) * src.count, s));
-        SW_HIP(outputs(n, nxt));
+        // with sources, a level is recorded by the next step's injection launch,
+        // the last one after it
+        const float *amp = io->wavelet ? io->wavelet + size_t(n) * src.count : nullptr;
+        if (src.count && rec.count)
+            SW_HIP(launch_points(src, amp, nxt, rec, owed ? cur : nullptr,
+                                 owed ? io->traces + size_t(n - 1) * rec.count : nullptr, s));
+        else if (src.count) SW_HIP(launch_inject(src, nxt, nullptr, amp, s));
         ++k;
+        owed = src.count && rec.count && k < nloop;
+        SW_HIP(outputs(n, nxt, !owed));
     }
     if (singly >= 0) return enqueue_multi2d<float>(p, run, singly, scratch, s);
     if (!ev.empty()) {

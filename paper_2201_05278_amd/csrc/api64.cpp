@@ -157,7 +157,8 @@ sw_status sw_forward_f64_scratch(sw_plan *p, const sw_fwd64_io *io, void *scratc
     const Run2D<double> run{ws, io->wavelet, {io->field[0], io->field[1]}, io->traces, io->snaps, nullptr,
                             io->saving_stride, 0, io->step0, io->nsteps_run};
     const int singly = multi2d_singles<double>(p, run, scratch, scratch_bytes);
-    for (int k = 0; k < (singly < 0 ? io->nsteps_run : singly); ++k) {
+    const int nloop = singly < 0 ? io->nsteps_run : singly;
+    for (int k = 0; k < nloop; ++k) {
         const int n = io->step0 + k;
         double *cur = io->field[k % 2];
         double *nxt = io->field[(k + 1) % 2];
@@ -166,8 +167,12 @@ sw_status sw_forward_f64_scratch(sw_plan *p, const sw_fwd64_io *io, void *scratc
         P.nxt = nxt;
         if (vec.tile >= 0) SW_HIP(launch_vec<double>(p->r, vec, MODE_FWD, P, s));
         else SW_HIP(launch_const64(p->r, p->ndim, t.tx, t.nw, P, s));
-        if (src.count) SW_HIP(launch_inject64(src, nxt, io->wavelet + size_t(n) * src.count, s));
-        if (rec.count) SW_HIP(launch_record64(rec, nxt, io->traces + size_t(n) * rec.count, s));
+        if (src.count && rec.count)      // the level of step n - 1, in cur, is recorded with this step's injection
+            SW_HIP(launch_points64(src, io->wavelet + size_t(n) * src.count, nxt, rec, k > 0 ? cur : nullptr,
+                                   k > 0 ? io->traces + size_t(n - 1) * rec.count : nullptr, s));
+        else if (src.count) SW_HIP(launch_inject64(src, nxt, io->wavelet + size_t(n) * src.count, s));
+        if (rec.count && (!src.count || k + 1 == nloop))
+            SW_HIP(launch_record64(rec, nxt, io->traces + size_t(n) * rec.count, s));
         if (io->snaps && io->saving_stride > 0 && (n + 1) % io->saving_stride == 0)
             SW_HIP(launch_snapshot64(g, nxt, io->snaps + size_t((n + 1) / io->saving_stride - 1) * p->grid_nodes,
                                      s));

@@ -128,10 +128,10 @@ sw_status batch_step(sw_batch *b, void *table, int k, bool points, hipStream_t s
         SW_HIP(launch_vec_batch(b->r, params, tiles, b->nshots, k % 2, persistent_blocks(b), s));
     else
         SW_HIP(launch_const_batch(b->r, b->ndim, bt, params, tiles, b->nshots, k % 2, persistent_blocks(b), s));
-    if (points) {
-        SW_HIP(launch_inject_batch(pts, b->nshots, b->max_uniq, b->max_per_node, k, k % 2, s));
-        SW_HIP(launch_record_batch(pts, b->nshots, b->max_rec, b->max_per_point, k, k % 2, s));
-    }
+    // a level is recorded with the next step's injection, the last one by the caller
+    if (points)
+        SW_HIP(launch_points_batch(pts, b->nshots, b->max_uniq, b->max_per_node, b->max_rec, b->max_per_point, k, k % 2,
+                                   s));
     return SW_OK;
 }
 
@@ -145,6 +145,10 @@ sw_status enqueue_batch(sw_batch *b, const sw_batch_io *io, hipStream_t s)
     for (int k = 0; k < io->nsteps_run; ++k) {
         sw_status st = batch_step(b, io->table, k, true, s);
         if (st != SW_OK) return st;
+    }
+    if (const int k = io->nsteps_run - 1; k >= 0) {
+        const auto *pts = reinterpret_cast<const ShotPoints *>(static_cast<char *>(io->table) + b->off_points);
+        SW_HIP(launch_record_batch(pts, b->nshots, b->max_rec, b->max_per_point, k, k % 2, s));
     }
     return SW_OK;
 }

@@ -197,12 +197,13 @@ struct ShotPoints {
 hipError_t launch_const_batch(int r, int ndim, const Tiling &t, const StencilParams *shots,
                               const int *tile_start, int nshots, int parity, int nblocks,
                               hipStream_t s);
-// Injection / recording for every shot of a batch at step `step`; the new
-// level is in field[parity ^ 1].
-hipError_t launch_inject_batch(const ShotPoints *shots, int nshots, int max_uniq, int max_per_node,
-                               int step, int parity, hipStream_t s);
+// Recording for every shot of a batch at step `step`; the new level is in
+// field[parity ^ 1].
 hipError_t launch_record_batch(const ShotPoints *shots, int nshots, int max_count, int max_per_point,
                                int step, int parity, hipStream_t s);
+// Injection at step `step` and recording of the level of step - 1 (none at step 0).
+hipError_t launch_points_batch(const ShotPoints *shots, int nshots, int max_uniq, int max_per_node, int max_count,
+                               int max_per_point, int step, int parity, hipStream_t s);
 
 hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t s);
 // *count = number of non-finite values among a[0 .. n) (count cleared first).
@@ -229,6 +230,10 @@ hipError_t launch_inject(const PointTableDev &t, float *field, float *store, con
 hipError_t launch_inject_values(const PointTableDev &t, const float *amp0, const float *amp1, float *out,
                                 hipStream_t s);
 hipError_t launch_record(const PointTableDev &t, const float *field, float *out, hipStream_t s);
+// Injection of a step into its new level nxt and, unless cur is NULL, recording
+// of the level cur before it, in one launch (points.h).
+hipError_t launch_points(const PointTableDev &src, const float *amp, float *nxt, const PointTableDev &rec,
+                         const float *cur, float *out, hipStream_t s);
 hipError_t launch_snapshot(const Geom &g, const float *field, float *out, hipStream_t s);
 // Fold dJ/dM from the extended grid onto the physical grid and scale by
 // 2 dt^2 c; tmp0 / tmp1 hold Z*X*ny and Z*nx*ny floats.

@@ -41,6 +41,8 @@ hipError_t launch_point_coef64(const PointTable64 &t, const double2 *damp, const
                                double scale, hipStream_t s);
 hipError_t launch_inject64(const PointTable64 &t, double *field, const double *amp, hipStream_t s);
 hipError_t launch_record64(const PointTable64 &t, const double *field, double *out, hipStream_t s);
+hipError_t launch_points64(const PointTable64 &src, const double *amp, double *nxt, const PointTable64 &rec,
+                           const double *cur, double *out, hipStream_t s);
 hipError_t launch_ghost64(const Geom &g, const int (*bcm)[2], int depth, double *field, hipStream_t s);
 hipError_t launch_snapshot64(const Geom &g, const double *field, double *out, hipStream_t s);
 hipError_t launch_const64(int r, int ndim, int tx, int nw, StencilParamsT<double> &P, hipStream_t s);

@@ -7,6 +7,7 @@
 
 #include "device64.h"
 #include "ghost.h"
+#include "points.h"
 
 namespace sw {
 
@@ -200,6 +201,12 @@ hipError_t launch_record64(const PointTable64 &t, const double *field, double *o
 }
 
 #undef SW_G64
+
+hipError_t launch_points64(const PointTable64 &src, const double *amp, double *nxt, const PointTable64 &rec,
+                           const double *cur, double *out, hipStream_t s)
+{
+    return launch_points_t<double>(src, amp, nxt, rec, cur, out, s);
+}
 
 hipError_t launch_ghost64(const Geom &g, const int (*bcm)[2], int depth, double *field, hipStream_t s)
 {

@@ -8,6 +8,7 @@
 // node or receiver and finish with a butterfly reduction inside the group.
 #include "device.h"
 #include "ghost.h"
+#include "points.h"
 
 #include <mutex>
 
@@ -214,25 +215,6 @@ __global__ void __launch_bounds__(kBlock) k_record(PointTableDev t, const float 
 
 // Batched versions: blockIdx.y selects the shot.
 template <int G>
-__global__ void __launch_bounds__(kBlock) k_inject_batch(const ShotPoints *__restrict__ shots, int step,
-                                                         int parity)
-{
-    const ShotPoints &S = shots[blockIdx.y];
-    const PointTableDev &t = S.src;
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int u = gid / G, sub = gid % G;
-    const float *amp = S.wavelet + size_t(step) * t.count;
-    float sa = 0.0f;
-    if (u < t.nuniq)
-        for (int k = t.uptr[u] + sub; k < t.uptr[u + 1]; k += G) {
-            const int e = t.uent[k];
-            sa = fmaf(t.coef_a[e], amp[t.pid[e]], sa);
-        }
-    sa = group_sum<G>(sa);
-    if (u < t.nuniq && sub == 0) S.field[parity ^ 1][t.unode[u]] += sa;
-}
-
-template <int G>
 __global__ void __launch_bounds__(kBlock) k_record_batch(const ShotPoints *__restrict__ shots, int step,
                                                          int parity)
 {
@@ -246,6 +228,20 @@ __global__ void __launch_bounds__(kBlock) k_record_batch(const ShotPoints *__res
         for (int e = t.ptr[pt] + sub; e < t.ptr[pt + 1]; e += G) acc += t.wscaled[e] * field[t.node[e]];
     acc = group_sum<G>(acc);
     if (pt < t.count && sub == 0) S.traces[size_t(step) * t.count + pt] = acc;
+}
+
+// As k_points, for the shots of a batch.
+__global__ void __launch_bounds__(kBlock) k_points_batch(const ShotPoints *__restrict__ shots, int nsb, int gs, int gr,
+                                                         int step, int parity)
+{
+    const ShotPoints &S = shots[blockIdx.y];
+    const int b = blockIdx.x;
+    if (b < nsb)
+        inject_group<float>(S.src, b * kBlock + threadIdx.x, gs, S.wavelet + size_t(step) * S.src.count,
+                            S.field[parity ^ 1]);
+    else
+        record_group<float>(S.rec, (b - nsb) * kBlock + threadIdx.x, gr, S.field[parity],
+                            S.traces + size_t(step - 1) * S.rec.count);
 }
 
 __global__ void k_snapshot(Geom g, const float *__restrict__ f, float *__restrict__ out)
@@ -397,6 +393,12 @@ hipError_t launch_inject(const PointTableDev &t, float *field, float *store, con
     return hipGetLastError();
 }
 
+hipError_t launch_points(const PointTableDev &src, const float *amp, float *nxt, const PointTableDev &rec,
+                         const float *cur, float *out, hipStream_t s)
+{
+    return launch_points_t<float>(src, amp, nxt, rec, cur, out, s);
+}
+
 hipError_t launch_record(const PointTableDev &t, const float *field, float *out, hipStream_t s)
 {
     if (t.count <= 0) return hipSuccess;
@@ -425,21 +427,22 @@ hipError_t launch_inject_values(const PointTableDev &t, const float *amp0, const
     return hipGetLastError();
 }
 
-hipError_t launch_inject_batch(const ShotPoints *shots, int nshots, int max_uniq, int max_per_node,
-                               int step, int parity, hipStream_t s)
-{
-    if (max_uniq <= 0 || nshots <= 0) return hipSuccess;
-    const int G = group_size(max_per_node);
-    SW_GROUP_DISPATCH2(G, k_inject_batch, max_uniq, nshots, s, shots, step, parity);
-    return hipGetLastError();
-}
-
 hipError_t launch_record_batch(const ShotPoints *shots, int nshots, int max_count, int max_per_point,
                                int step, int parity, hipStream_t s)
 {
     if (max_count <= 0 || nshots <= 0) return hipSuccess;
     const int G = group_size(max_per_point);
     SW_GROUP_DISPATCH2(G, k_record_batch, max_count, nshots, s, shots, step, parity);
+    return hipGetLastError();
+}
+
+hipError_t launch_points_batch(const ShotPoints *shots, int nshots, int max_uniq, int max_per_node, int max_count,
+                               int max_per_point, int step, int parity, hipStream_t s)
+{
+    const int gs = group_size(max_per_node), gr = group_size(max_per_point);
+    const int nsb = point_blocks(max_uniq, gs), nrb = step > 0 ? point_blocks(max_count, gr) : 0;
+    if (nsb + nrb == 0 || nshots <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_points_batch, dim3(nsb + nrb, nshots), dim3(kBlock), 0, s, shots, nsb, gs, gr, step, parity);
     return hipGetLastError();
 }
 
