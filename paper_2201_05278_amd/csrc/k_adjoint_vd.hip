@@ -25,10 +25,6 @@ namespace {
 
 constexpr int kBlock = 256;
 
-struct AxisCoef {
-    float s[11];    // s_j / h along the axis
-};
-
 struct MidCoef {
     float m[11];    // midpoint interpolation weights m_j
 };
@@ -42,38 +38,51 @@ int grid_blocks(int64_t n)
 }
 
 // Faces outside the grid's node range, one thread each: m = -r .. -1 and
-// m = n .. n + r - 2 along `axis` (the 2r - 1 faces that no grid node owns),
+// m = n .. n + r - 2 along each axis (the 2r - 1 faces that no grid node owns),
 // the grid along the other two axes.  The face sum of face m lives at the
-// padded position of node m, inside the stored halo.
-__global__ void k_face_image_outer(Geom g, int axis, int r, AxisCoef c, const float *__restrict__ phi,
-                                   const float *__restrict__ u, float *__restrict__ F)
+// padded position of node m, inside the stored halo.  One launch takes every
+// axis and level pair (up to six single ones before: 53 us per two adjoint steps
+// at 240^3 SO8, this one 33; bound by the chain of loads of each face).
+struct OuterFaces {
+    float s[3][11];                 // s_j / h per axis
+    const float *phi[2], *u[2];     // level pairs, accumulated in this order
+    float *F[3];
+    int64_t end[3];                 // items of axes 0 .. a
+    int np, r;
+};
+
+__global__ void k_face_image_outer(Geom g, OuterFaces c)
 {
     const int n[3] = {g.Z, g.X, g.Y};
-    int e[3] = {n[0], n[1], n[2]};
-    e[axis] = 2 * r - 1;
-    const int64_t total = int64_t(e[0]) * e[1] * e[2];
-    for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < total;
-         i += int64_t(gridDim.x) * blockDim.x) {
+    const int r = c.r;
+    for (int64_t i0 = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i0 < c.end[2];
+         i0 += int64_t(gridDim.x) * blockDim.x) {
+        const int axis = i0 < c.end[0] ? 0 : i0 < c.end[1] ? 1 : 2;
+        const int64_t i = i0 - (axis == 0 ? 0 : axis == 1 ? c.end[0] : c.end[1]);
+        const int ex = axis == 1 ? 2 * r - 1 : g.X, ey = axis == 2 ? 2 * r - 1 : g.Y;
         int k[3];
-        k[2] = int(i % e[2]);
-        const int64_t t = i / e[2];
-        k[1] = int(t % e[1]);
-        k[0] = int(t / e[1]);
-        k[axis] = (k[axis] < r) ? k[axis] - r : n[axis] + k[axis] - r;   // face index m
-        const int m = k[axis];
-        auto at = [&](const float *f, int v) -> float {  // node v along the axis, zero off the grid
-            if (v < 0 || v >= n[axis]) return 0.0f;
-            int q[3] = {k[0], k[1], k[2]};
-            q[axis] = v;
-            return f[elem(g, q[0], q[1], q[2])];
-        };
-        float dp = 0.0f, du = 0.0f;
-        for (int l = 1; l <= r; ++l) {
-            dp = fmaf(c.s[l], at(phi, m + l) - at(phi, m - l + 1), dp);
-            du = fmaf(c.s[l], at(u, m + l) - at(u, m - l + 1), du);
+        k[2] = int(i % ey);
+        const int64_t t = i / ey;
+        k[1] = int(t % ex);
+        k[0] = int(t / ex);
+        const int q = axis == 0 ? k[0] : axis == 1 ? k[1] : k[2], na = axis == 0 ? n[0] : axis == 1 ? n[1] : n[2];
+        const int m = q < r ? q - r : na + q - r;                    // face index
+        const int64_t step = axis == 0 ? int64_t(g.px) * g.py : axis == 1 ? g.py : 1;
+        const int64_t o = elem(g, axis == 0 ? m : k[0], axis == 1 ? m : k[1], axis == 2 ? m : k[2]);
+        float sum = c.F[axis][o];
+        for (int p = 0; p < c.np; ++p) {
+            const float *phi = c.phi[p], *u = c.u[p];
+            float dp = 0.0f, du = 0.0f;
+            for (int l = 1; l <= r; ++l) {                           // nodes m + l and m - l + 1, zero off the grid
+                const int hi = m + l, lo = m - l + 1;
+                const bool hin = hi >= 0 && hi < na, lin = lo >= 0 && lo < na;
+                const int64_t oh = o + l * step, ol = o - (l - 1) * step;
+                dp = fmaf(c.s[axis][l], (hin ? phi[oh] : 0.0f) - (lin ? phi[ol] : 0.0f), dp);
+                du = fmaf(c.s[axis][l], (hin ? u[oh] : 0.0f) - (lin ? u[ol] : 0.0f), du);
+            }
+            sum = fmaf(-dp, du, sum);
         }
-        const int64_t o = elem(g, k[0], k[1], k[2]);
-        F[o] = fmaf(-dp, du, F[o]);
+        c.F[axis][o] = sum;
     }
 }
 
@@ -369,19 +378,23 @@ hipError_t launch_face_image(const Geom &g, int ndim, int r, const float *const 
     case 9: launch_face_tile<9>(ndim, np, T, s); break;
     default: launch_face_tile<10>(ndim, np, T, s); break;
     }
-    // faces no grid node owns (m < 0 or m >= n along each axis), pair by pair
+    // faces no grid node owns (m < 0 or m >= n along each axis)
     const int n[3] = {g.Z, g.X, g.Y};
-    for (int k = 0; k < np; ++k)
-        for (int axis = 0; axis < 3; ++axis) {
-            if (ndim == 2 && axis == 1) continue;
-            AxisCoef c{};
-            for (int l = 1; l <= r; ++l) c.s[l] = sj[axis][l];
-            int e[3] = {n[0], n[1], n[2]};
-            e[axis] = 2 * r - 1;
-            const int64_t total = int64_t(e[0]) * e[1] * e[2];
-            hipLaunchKernelGGL(k_face_image_outer, dim3(grid_blocks(total)), dim3(kBlock), 0, s, g, axis, r, c,
-                               phi[k], u[k], F[axis]);
-        }
+    OuterFaces o{};
+    int64_t total = 0;
+    for (int axis = 0; axis < 3; ++axis) {
+        if (ndim == 3 || axis != 1) total += int64_t(2 * r - 1) * n[(axis + 1) % 3] * n[(axis + 2) % 3];
+        o.end[axis] = total;
+        o.F[axis] = F[axis];
+        for (int l = 1; l <= r; ++l) o.s[axis][l] = sj[axis][l];
+    }
+    for (int k = 0; k < np; ++k) {
+        o.phi[k] = phi[k];
+        o.u[k] = u[k];
+    }
+    o.np = np;
+    o.r = r;
+    hipLaunchKernelGGL(k_face_image_outer, dim3(grid_blocks(total)), dim3(kBlock), 0, s, g, o);
     return hipGetLastError();
 }
 

@@ -89,6 +89,23 @@ __global__ void k_copy(float *__restrict__ d, const float *__restrict__ s, int64
         d[i] = s[i];
 }
 
+// The same for 16-byte aligned arrays, four vectors in flight per thread; the
+// copies (checkpoints) go past the caches, which the next step wants (400^3: 109
+// us, 5.1 TB/s read and written, against 144 us one value at a time).
+typedef float Float4 __attribute__((ext_vector_type(4)));
+
+__global__ void __launch_bounds__(kBlock) k_copy4(Float4 *__restrict__ d, const Float4 *__restrict__ s, int64_t n4)
+{
+    const int64_t i = blockIdx.x * int64_t(4 * kBlock) + threadIdx.x;
+    Float4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (i + k * kBlock < n4) v[k] = __builtin_nontemporal_load(s + i + k * kBlock);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (i + k * kBlock < n4) __builtin_nontemporal_store(v[k], d + i + k * kBlock);
+}
+
 // Every element of the padded arrays receives a model value: the physical
 // node nearest to its model node (edge replication into the layer; mirror
 // images in the ghosts of mirrored sides; nearest node in the other ghosts and
@@ -275,26 +292,27 @@ __global__ void k_fold_axis(Geom g, int pass, const float *__restrict__ in, floa
     const int ox = (pass >= 1) ? g.np[1] : g.X;
     const int oy = g.np[2];
     (void)iz;
-    const int64_t total = int64_t(oz) * ox * oy;
-    for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < total;
-         i += int64_t(gridDim.x) * blockDim.x) {
-        const int y = int(i % oy);
-        const int64_t t = i / oy;
-        const int x = int(t % ox);
-        const int z = int(t / ox);
-        const int ax = (pass == 0) ? 2 : (pass == 1 ? 1 : 0);      // axis folded in this pass
-        const int c = (ax == 2) ? y : (ax == 1 ? x : z);           // physical index on that axis
-        const int ext = (ax == 2) ? g.Y : (ax == 1 ? g.X : g.Z);
-        int a = c + g.lo[ax], b = a;
-        if (c == 0) a = 0;
-        if (c == g.np[ax] - 1) b = ext - 1;
-        float s = 0.0f;
-        for (int k = a; k <= b; ++k) {
-            if (pass == 0) s += in[elem(g, z, x, k)];
-            else if (pass == 1) s += in[(int64_t(z) * ix + k) * iy + y];
-            else s += in[(int64_t(k) * ix + x) * iy + y];
+    // a wavefront takes a row of the output: one division per row, not per value
+    const int64_t rows = int64_t(oz) * ox;
+    const int lane = threadIdx.x & 63;
+    for (int64_t row = blockIdx.x * int64_t(kBlock / 64) + (threadIdx.x >> 6); row < rows;
+         row += int64_t(gridDim.x) * (kBlock / 64)) {
+        const int z = int(row / ox), x = int(row % ox);
+        for (int y = lane; y < oy; y += 64) {
+            const int64_t i = row * oy + y;
+            const int ax = (pass == 0) ? 2 : (pass == 1 ? 1 : 0);      // axis folded in this pass
+            const int c = (ax == 2) ? y : (ax == 1 ? x : z);           // physical index on that axis
+            const int ext = (ax == 2) ? g.Y : (ax == 1 ? g.X : g.Z);
+            int a = c + g.lo[ax], b = a;
+            if (c == 0) a = 0;
+            if (c == g.np[ax] - 1) b = ext - 1;
+            const float *from = pass == 0 ? in + elem(g, z, x, 0)
+                                : pass == 1 ? in + int64_t(z) * ix * iy + y : in + int64_t(x) * iy + y;
+            const int64_t step = pass == 0 ? 1 : pass == 1 ? iy : int64_t(ix) * iy;
+            float s = 0.0f;
+            for (int k = a; k <= b; ++k) s += from[k * step];
+            out[i] = (pass == 2 && vel) ? s * two_dt2 * vel[i] : s;
         }
-        out[i] = (pass == 2 && vel) ? s * two_dt2 * vel[i] : s;
     }
 }
 
@@ -333,7 +351,15 @@ hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t s)
 hipError_t launch_copy(float *dst, const float *src, int64_t n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_copy, dim3(blocks_for(n)), dim3(kBlock), 0, s, dst, src, n);
+    int64_t done = 0;
+    const int64_t blocks = (n / 4 + 4 * kBlock - 1) / (4 * kBlock);
+    if ((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) % 16 == 0 && blocks > 0 && blocks < (1 << 30)) {
+        hipLaunchKernelGGL(k_copy4, dim3(unsigned(blocks)), dim3(kBlock), 0, s, reinterpret_cast<Float4 *>(dst),
+                           reinterpret_cast<const Float4 *>(src), n / 4);
+        done = n / 4 * 4;
+    }
+    if (done < n)
+        hipLaunchKernelGGL(k_copy, dim3(blocks_for(n - done)), dim3(kBlock), 0, s, dst + done, src + done, n - done);
     return hipGetLastError();
 }
 
@@ -457,9 +483,7 @@ hipError_t launch_fold_gradient(const Geom &g, const float *grad_m, const float 
                                 float *grad_vel, float *tmp0, float *tmp1, hipStream_t s)
 {
     const float two_dt2 = float(2.0 * dt * dt);
-    const int64_t n0 = int64_t(g.Z) * g.X * g.np[2];
-    const int64_t n1 = int64_t(g.Z) * g.np[1] * g.np[2];
-    const int64_t n2 = int64_t(g.np[0]) * g.np[1] * g.np[2];
+    const int64_t n0 = int64_t(g.Z) * g.X * 64, n1 = int64_t(g.Z) * g.np[1] * 64, n2 = int64_t(g.np[0]) * g.np[1] * 64;
     hipLaunchKernelGGL(k_fold_axis, dim3(blocks_for(n0)), dim3(kBlock), 0, s, g, 0, grad_m, tmp0, vel, two_dt2);
     hipLaunchKernelGGL(k_fold_axis, dim3(blocks_for(n1)), dim3(kBlock), 0, s, g, 1, tmp0, tmp1, vel, two_dt2);
     hipLaunchKernelGGL(k_fold_axis, dim3(blocks_for(n2)), dim3(kBlock), 0, s, g, 2, tmp1, grad_vel, vel, two_dt2);

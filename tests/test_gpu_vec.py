@@ -96,3 +96,30 @@ def test_batch_on_vector_tiles_is_bitwise_scalar_tiles(so):
     for other in out[1:]:
         for x, y in zip(out[0], other):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("scheme,dtype", [("const", "float32"), ("const", "float64"), ("vd_staggered", "float32"),
+                                          ("vd_centred", "float32")])
+def test_wavefields_at_any_element_of_a_buffer(scheme, dtype):
+    """Buffers that start between 16-byte boundaries: same levels, traces and checkpoints."""
+    from paper_2201_05278_amd import Propagator, critical_dt, ricker
+    print(f"case: wavefields off the vector alignment {scheme} {dtype}", flush=True)
+    n, h, steps, out = (40, 37, 70), (10.0, 10.0, 10.0), 9, []
+    dt = 0.5 * critical_dt(h, 8, 3000.0)
+    prop = Propagator(n, h, 8, dt, steps, scheme=scheme, nbl=6, dtype=dtype)
+    prop.set_sources([[195.0, 180.0, 345.0]], "linear")
+    prop.set_receivers([[195.0, 180.0, 345.0], [100.0, 90.0, 300.0]], "linear")
+    rng = np.random.default_rng(2)
+    vel = torch.from_numpy(rng.uniform(1500.0, 3000.0, n)).to(prop.torch_dtype)
+    rho = torch.from_numpy(rng.uniform(1000.0, 2000.0, n)).float()
+    prop.prepare(vel, *(() if scheme == "const" else (rho,)), cmax=3000.0)
+    size = prop.layout.field_elems
+    every = 4 if dtype == "float32" and scheme != "vd_centred" else 0
+    for off in (0, 1, 3):
+        f = [torch.zeros(size + 4, dtype=prop.torch_dtype, device="cuda")[off:off + size] for _ in range(2)]
+        r = prop.forward(ricker(30.0, dt, steps).reshape(-1, 1), fields=tuple(f), checkpoint_every=every)
+        out.append([r.traces.clone(), *f] + ([r.ckpt] if every else []))
+    assert float(out[0][0].abs().max()) > 0.0
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert torch.equal(a, b)
