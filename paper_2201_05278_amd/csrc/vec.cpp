@@ -131,7 +131,8 @@ namespace {
 // and a tile that has the CU to itself waits at their second barrier with
 // nothing else to run.  So tiles are taken there of which two fit and whose
 // waves spread evenly over the SIMDs (207 x 801 x 801, SO8: 24 x 64 columns
-// 0.566 ms, 16 x 64 0.429; in doubles 24 x 64 0.957, 16 x 64 0.861).
+// 0.566 ms, 16 x 64 0.429; in doubles 24 x 64 0.957, 16 x 64 0.861).  Imaging
+// launches, with up to seven streams, want the even spread too.
 struct CostModel {
     double k, k1, a, c, hx, hy, w, tail, pm, latency, idle, edge;
 };
@@ -150,6 +151,7 @@ VecChoice choose(const sw_plan *p, int mode)
     const int Z = p->dims[0], X = p->dims[1], Y = p->dims[2], R = p->r;
     const int64_t pbytes = int64_t(p->pad[1]) * p->pad[2] * int64_t(sizeof(T));
     const bool edges = p->prob.bc[1][0] || p->prob.bc[1][1] || p->prob.bc[2][0] || p->prob.bc[2][1];
+    const bool image = mode == MODE_IMAGE || mode == MODE_IMAGE2;
     const int zmax = int(std::max<int64_t>(1, (int64_t(1) << 31) / pbytes - 4 * R - 2));
     double cost = 0.0;
     for (int i = 0; i < kVecTileCount; ++i) {
@@ -158,7 +160,7 @@ VecChoice choose(const sw_plan *p, int mode)
         // resident blocks, with a block's waves spread over the four SIMDs (6
         // waves take two slots of each of two SIMDs)
         const int res = std::min(resident<T>(R, i, mode), waves >= 4 ? slots / ((waves + 3) / 4) : slots * 4 / waves);
-        if (res <= 0 || (edges && slots >= 4 && (res < 2 || (waves > 2 && waves % 4)))) continue;
+        if (res <= 0 || (slots >= 4 && (edges || image) && waves > 2 && waves % 4) || (slots >= 4 && edges && res < 2)) continue;
         const double tiles = double((X + t.tx - 1) / t.tx) * ((Y + cols - 1) / cols);
         const double used = double(X) * Y / (tiles * t.tx * cols);
         const double nodes = t.tx * cols * (sizeof(T) / 4.0) * (used + (1.0 - used) * m.idle);
