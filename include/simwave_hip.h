@@ -332,7 +332,10 @@ typedef struct sw_adj_io {
  * The centred variable-density scheme and mirror ghosts: SW_ERR_UNSUPPORTED. */
 sw_status sw_adjoint(sw_plan *plan, const sw_adj_io *io, void *stream);
 
-/* Stencil tiling of a plan.  Results never depend on it.
+/* Stencil tiling of a plan.  Results never depend on it.  A 3D plan whose
+ * tiling is left at the defaults runs vector tiles where those are faster (16
+ * bytes of columns per thread; tile and z chunk from a cost model of the
+ * launch); any field set here makes it run the tiles described below.
  *   tx, nw  rows per block and waves per block.  3D constant density:
  *           block tiles (16,4), (8,4), (32,8), (16,8), (8,8), (24,8), or with wt = 1
  *           wave tiles (16,4), (32,4), (4,1), (8,1), (16,2) (each wave owns
@@ -368,15 +371,16 @@ typedef struct sw_tiling {
  * only: wave tiles, two-step sweeps and occupancy caps are refused, and the
  * cache policy, prefetch depth and block order are ignored. */
 sw_status sw_plan_set_tiling(sw_plan *plan, const sw_tiling *t);
-/* The tiling the plan's stencil launches use (defaults resolved).  For 3D
+/* The block tiling of the plan (defaults resolved): what its launches use
+ * unless they run vector tiles, as 3D defaults do (see sw_tiling).  For 3D
  * block tiles in single precision on a device (every scheme), the default
  * z chunk is the one with the fewest whole rounds of resident blocks times
  * planes per block (chunks of 4r .. 100 planes making at least three rounds);
  * elsewhere (and without a device, or where no chunk qualifies) about 16000
  * waves per launch, chunks of at most 74 planes. */
 sw_status sw_plan_get_tiling(const sw_plan *plan, sw_tiling *out);
-/* Resident blocks per compute unit of the plan's stencil kernel under its
- * current tiling (the runtime's occupancy calculator) and the device's
+/* Resident blocks per compute unit of the plan's block-tile kernel under its
+ * current tiling, as sw_plan_get_tiling reports it (the runtime's occupancy calculator) and the device's
  * compute units: set for 3D block tiles (every scheme and precision), 0
  * and 0 otherwise or without a device. */
 sw_status sw_plan_occupancy(const sw_plan *plan, int32_t *blocks_per_cu, int32_t *cus);
@@ -388,8 +392,8 @@ typedef struct sw_batch sw_batch;
 /* Group `nshots` prepared constant-density plans (each with its own grid
  * size, dt, model, geometry and workspace; all with the same ndim, space
  * order and step count) so that every time step advances all shots with one
- * stencil launch over a tile list spanning all shots, one batched
- * injection and one batched recording launch.  The plans stay owned by the
+ * stencil launch over a tile list spanning all shots and one launch
+ * that injects the step and records the one before.  The plans stay owned by the
  * caller and must outlive the batch. */
 sw_status sw_batch_create(int32_t nshots, sw_plan *const *plans, sw_batch **out);
 sw_status sw_batch_destroy(sw_batch *batch);
@@ -430,7 +434,7 @@ sw_status sw_batch_forward(sw_batch *batch, const sw_batch_io *io, void *stream)
  * serialised by the caller.  Results are bitwise those of sw_batch_forward. */
 sw_status sw_batch_forward_static(sw_batch *batch, const sw_batch_io *io, void *stream);
 
-/* Pick the tile shape (rows per tile, waves per block), the z-chunk length,
+/* Pick the library's default (3D: vector tiles), or the tile shape (rows per tile, waves per block), the z-chunk length,
  * cache policy and prefetch depth, for single plans also the two-step sweep
  * (when io->field2 is given) and a cap of 4 resident blocks per CU, and (for
  * batches) the launch grid (one block per tile or a looping grid), by timing a few steps of each

@@ -1,5 +1,5 @@
 // Batched shots (one stencil launch per step over a tile list spanning all
-// shots, one batched injection and one batched recording) and the autotuner of
+// shots, one launch that injects and records) and the autotuner of
 // tile shape, z-chunk length, cache policy and launch grid.
 #include <algorithm>
 #include <cmath>
@@ -116,7 +116,7 @@ sw_status upload_table(sw_batch *b, void *table, hipStream_t s)
     return SW_OK;
 }
 
-// One batched step k: stencil for every shot, then injection and recording.
+// One batched step k: stencil for every shot, then its injection and the recording of step k - 1.
 sw_status batch_step(sw_batch *b, void *table, int k, bool points, hipStream_t s)
 {
     char *t = static_cast<char *>(table);

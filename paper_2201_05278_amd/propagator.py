@@ -458,8 +458,8 @@ class Propagator:
 
 class Batch:
     """Many prepared constant-density propagators (shots) advanced together:
-    one persistent stencil launch per step over the tiles of all shots, one
-    batched injection and one batched recording launch."""
+    one persistent stencil launch per step over the tiles of all shots and one
+    that injects the step and records the one before."""
 
     def __init__(self, props):
         self.props = list(props)
