@@ -3,7 +3,7 @@
 // only reads it, so its receivers need not be recorded before that launch: they
 // go with the next step's injection, which writes the other buffer.  On small
 // grids the two point launches were half of a step (83 x 97 x 101 and its layer,
-// SO4: 4.3 and 4.9 us of 19.2 us per step); what bounds them is their own chain of
+// SO4: 4.3 and 4.9 us of 19.2 us per step; 16.8 with one); what bounds them is their own chain of
 // loads (entry, node, value) and the gap between dependent launches, so that
 // one launch for both costs what the longer one did.
 #pragma once

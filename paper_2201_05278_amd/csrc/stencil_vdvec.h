@@ -5,12 +5,19 @@
 //
 // A block owns TX rows x TY = LPR * CW columns, one thread per vector.  The
 // scalar tiles issue a load, an LDS access and its address for every value, and
-// the instruction stream, not memory, sets their pace (592^3 SO8 staggered 1367
-// us per step for 20 bytes per node, which take 740 us at the card's rate).
-// With vectors the loads and LDS instructions per node drop to a quarter, and
-// queue entries rotate through registers without moves.
+// the instruction stream, not memory, sets their pace.  With vectors the loads
+// and LDS instructions per node drop to a quarter, and queue entries rotate
+// through registers without moves.
+// What bounds them: instructions.  Staggered, 592^3 SO8: 113 vector instructions
+// per node keep the SIMDs 45% busy and LDS 31%, in phases that a block's barriers
+// keep apart, 1.318 ms per step (scalar tiles 1.361; 20 bytes per node at the
+// card's rate take 0.74); 240^3 104 against 122 us.  Centred, 280^3 SO8: 98 per
+// node, three quarters of the issue slots of a SIMD that holds two waves, 130
+// against 156 us.
 // CW is 4 up to R = 4 (staggered) and R = 6 (centred), else 2: three (two)
-// queues of 2R vectors of 4 would not leave two waves per SIMD their registers.
+// queues of 2R vectors of 4 would not leave two waves per SIMD their registers
+// (two columns per thread at R = 4, held to four waves, ran no faster: centred
+// 136 us, staggered spilled, 288).
 //
 // The wavefield's mirror ghosts and the model's ghosts are read from the stored
 // halo.  A vector that the grid ends in is cut where nothing lies beyond (no

@@ -190,7 +190,8 @@ VecChoice choose(const sw_plan *p, int mode)
 // that fill a round march together and each further round costs as much again,
 // a last partial one a little less where its blocks have a SIMD to themselves
 // (fitted to sweeps on six grids of 2.7 M .. 207 M nodes at SO4, SO8 and SO16:
-// its choices ran within 2% of the sweep's best on average).
+// its choices ran within 1% of the sweep's best on average, staggered, and 3%,
+// centred).
 struct VdCost {
     double hx, hy, warm, plane, tail, alone, last;
 };
