@@ -324,23 +324,26 @@ class Propagator:
             self._field2 = (self.new_field(), self.new_field())
         return self._field2
 
-    def _scratch(self, use_graph):
-        """Device scratch of a forward, or None.  One per call, so that runs of one
-        plan may overlap on several streams; a graph keeps its own, since it is
-        replayed only on the buffers it was captured with."""
+    def _scratch(self, graph):
+        """Device scratch of a forward, or None.  Launches (graph False) take one per
+        call, so that runs of one plan may overlap on several streams.  A graph is
+        replayed on the buffers it was captured with: its scratch is kept with the
+        wavefields that it writes (graph: the two buffers), and a graph over other
+        wavefields, which may overlap with it, gets another."""
         n = ctypes.c_int64(0)
         L.check("sw_plan_scratch", L.lib().sw_plan_scratch(self._plan, ctypes.byref(n)))
         if n.value == 0:
             return None
-        kept = getattr(self, "_graph_scratch", None) if use_graph else None
-        if kept is None or kept.numel() != n.value:
+        key = tuple(f.data_ptr() for f in graph) + (n.value,) if graph else None
+        kept_key, kept = getattr(self, "_graph_scratch", (None, None))
+        if key is None or kept_key != key:
             try:
                 kept = torch.empty(n.value, dtype=torch.uint8, device=self.device)
             except torch.cuda.OutOfMemoryError:
                 return None                     # the single-step kernels need none
-        if use_graph:
+        if key is not None:
             kept.record_stream(torch.cuda.current_stream(self.device))
-            self._graph_scratch = kept
+            self._graph_scratch = (key, kept)
         return kept
 
     def _fwd_io(self, wavelet, fields, traces):
@@ -405,7 +408,7 @@ class Propagator:
         spare = self._spare_fields()
         if spare is not None:
             io.field2[0], io.field2[1] = spare[0].data_ptr(), spare[1].data_ptr()
-        scratch = self._scratch(use_graph)
+        scratch = self._scratch(fields if use_graph else False)
         self._keep = (wavelet, fields, traces, snaps, ckpt, scratch)
         L.check("sw_forward", L.lib().sw_forward_scratch(
             self._plan, ctypes.byref(io), _ptr(scratch), scratch.numel() if scratch is not None else 0, _stream()))
