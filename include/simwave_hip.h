@@ -371,6 +371,31 @@ typedef struct sw_tiling {
  * only: wave tiles, two-step sweeps and occupancy caps are refused, and the
  * cache policy, prefetch depth and block order are ignored. */
 sw_status sw_plan_set_tiling(sw_plan *plan, const sw_tiling *t);
+/* What a plan's stencil launches run in one role: */
+enum { SW_ROLE_FORWARD = 0,     /* forward steps, and the adjoint's steps that image nothing */
+       SW_ROLE_RECOMPUTE = 1,   /* sw_adjoint: steps recomputed from a checkpoint */
+       SW_ROLE_IMAGE = 2,       /* sw_adjoint: a step that images one level ... */
+       SW_ROLE_IMAGE_PAIR = 3   /* ... or two */ };
+enum { SW_TILES_BLOCK = 0,      /* block or wave tiles (sw_plan_get_tiling) */
+       SW_TILES_VECTOR = 1,     /* 3D vector tiles */
+       SW_TILES_STEPS = 2       /* 2D tiles that advance several steps (with scratch; the
+                                   calls that run singly are listed at sw_forward_scratch) */ };
+typedef struct sw_launch {
+    int32_t kind;               /* SW_TILES_* */
+    int32_t tile;               /* index among the tiles of kind 1 or 2, else -1 */
+    int32_t rows, cols;         /* output nodes per block along x (2D: z) and along the last axis */
+    int32_t zc;                 /* z-chunk length (kind 2: 0) */
+    int32_t steps;              /* time steps per launch */
+} sw_launch;
+sw_status sw_plan_get_launch(const sw_plan *plan, int32_t role, sw_launch *out);
+/* Make a role of a plan with the default tiling run vector tile `tile` with a z
+ * chunk of `extent` planes (3D), or multi-step tile `tile` with `extent` steps
+ * per launch (2D), in place of the library's choice; tile -1: back to it.
+ * Results never depend on it.  SW_ERR_UNSUPPORTED for a tile that the plan's
+ * scheme, order, precision and role do not have, SW_ERR_STATE for a plan with a
+ * tiling of its own; sw_plan_set_tiling takes every role back to the library's
+ * choice. */
+sw_status sw_plan_set_launch(sw_plan *plan, int32_t role, int32_t tile, int32_t extent);
 /* The block tiling of the plan (defaults resolved): what its launches use
  * unless they run vector tiles, as 3D defaults do (see sw_tiling).  For 3D
  * block tiles in single precision on a device (every scheme), the default

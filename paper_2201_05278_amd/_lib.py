@@ -22,6 +22,8 @@ SW_INTERP_HICKS, SW_INTERP_LINEAR = 0, 1
 SCHEMES = {"const": SW_CONST, "vd_staggered": SW_VD_STAGGERED, "vd_centred": SW_VD_CENTRED}
 INTERPS = {"hicks": SW_INTERP_HICKS, "linear": SW_INTERP_LINEAR}
 BCS = {"none": 0, "dirichlet": 1, "neumann": 2}
+ROLES = {"forward": 0, "recompute": 1, "image": 2, "image_pair": 3}
+TILE_KINDS = ("block", "vector", "steps")
 
 STATUS = {0: "SW_OK", 1: "SW_ERR_ARG", 2: "SW_ERR_UNSUPPORTED", 3: "SW_ERR_DOMAIN",
           4: "SW_ERR_CFL", 5: "SW_ERR_STATE", 6: "SW_ERR_WORKSPACE", 7: "SW_ERR_HIP",
@@ -77,6 +79,11 @@ class Tiling(ctypes.Structure):
                 ("wt", c_int32), ("ts", c_int32), ("occ", c_int32), ("order", c_int32)]
 
 
+class Launch(ctypes.Structure):
+    _fields_ = [("kind", c_int32), ("tile", c_int32), ("rows", c_int32), ("cols", c_int32), ("zc", c_int32),
+                ("steps", c_int32)]
+
+
 class BatchIO(ctypes.Structure):
     _fields_ = [("shots", ctypes.POINTER(FwdIO)), ("table", c_void_p), ("nsteps_run", c_int32),
                 ("use_graph", c_int32)]
@@ -108,6 +115,8 @@ SIGNATURES = {
     "sw_adjoint": (c_int32, [c_void_p, ctypes.POINTER(AdjIO), c_void_p]),
     "sw_plan_set_tiling": (c_int32, [c_void_p, ctypes.POINTER(Tiling)]),
     "sw_plan_get_tiling": (c_int32, [c_void_p, ctypes.POINTER(Tiling)]),
+    "sw_plan_get_launch": (c_int32, [c_void_p, c_int32, ctypes.POINTER(Launch)]),
+    "sw_plan_set_launch": (c_int32, [c_void_p, c_int32, c_int32, c_int32]),
     "sw_plan_occupancy": (c_int32, [c_void_p, ctypes.POINTER(c_int32), ctypes.POINTER(c_int32)]),
     "sw_batch_create": (c_int32, [c_int32, ctypes.POINTER(c_void_p), ctypes.POINTER(c_void_p)]),
     "sw_batch_destroy": (c_int32, [c_void_p]),

@@ -318,11 +318,9 @@ void set_tiles(const sw_plan *p, const Tiling &t, StencilParams &P)
     P.nzc = (p->dims[0] + P.zc - 1) / P.zc;
 }
 
-hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, const VecChoice &vec, hipStream_t s)
+// Block or wave tiles of a single-step launch in a mode.
+static Tiling mode_tiling(const sw_plan *p, int mode)
 {
-    if (vec.tile >= 0)
-        return p->prob.scheme == SW_CONST ? launch_vec<float>(p->r, vec, mode, P, s)
-                                          : launch_vdvec(p->prob.scheme, p->r, vec, mode, P, s);
     Tiling t = choose_tiling(p);
     t.ts = 1;
     // the staggered imaging stencil holds two more values per node than the
@@ -333,6 +331,15 @@ hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, const VecChoice
         t.tx = 8;
         t.nw = 8;
     }
+    return t;
+}
+
+hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, const VecChoice &vec, hipStream_t s)
+{
+    if (vec.tile >= 0)
+        return p->prob.scheme == SW_CONST ? launch_vec<float>(p->r, vec, mode, P, s)
+                                          : launch_vdvec(p->prob.scheme, p->r, vec, mode, P, s);
+    const Tiling t = mode_tiling(p, mode);
     set_tiles(p, t, P);
     if (p->prob.scheme == SW_CONST) return launch_const(p->r, p->ndim, mode, t, P, s);
     return launch_vd(p->prob.scheme, mode, p->r, p->ndim, t, P, s);
@@ -545,6 +552,7 @@ sw_status sw_plan_set_tiling(sw_plan *p, const sw_tiling *t)
         p->tile_tx = t->tx;
         p->tile_nw = t->nw;
         p->tile_zc = t->zc;
+        for (auto &pin : p->pin) pin = {};
         if (p->graph_exec) {
             (void)hipGraphExecDestroy(static_cast<hipGraphExec_t>(p->graph_exec));
             p->graph_exec = nullptr;
@@ -588,10 +596,60 @@ sw_status sw_plan_set_tiling(sw_plan *p, const sw_tiling *t)
     p->tile_ts = d.ts;
     p->tile_occ = d.occ;
     p->tile_order = d.order;
+    for (auto &pin : p->pin) pin = {};
     if (p->graph_exec) {
         (void)hipGraphExecDestroy(static_cast<hipGraphExec_t>(p->graph_exec));
         p->graph_exec = nullptr;
     }
+    return SW_OK;
+}
+
+sw_status sw_plan_set_launch(sw_plan *p, int32_t role, int32_t tile, int32_t extent)
+{
+    set_error("");
+    if (!p) return fail(SW_ERR_ARG, "plan is NULL");
+    if (role < 0 || role > 3) return fail(SW_ERR_ARG, "unknown role");
+    if (tile >= 0) {
+        if (!default_tiling(p)) return fail(SW_ERR_STATE, "the plan has a tiling of its own (sw_plan_set_tiling)");
+        if (p->ndim == 3) {
+            if (!vec_instance(p, role, tile)) return fail(SW_ERR_UNSUPPORTED, "no such vector tile for this plan and role");
+            if (extent < 1 || extent > vec_zmax(p)) return fail(SW_ERR_ARG, "z chunk outside 1 .. the longest window");
+        } else if (p->prob.scheme != SW_CONST || role != SW_ROLE_FORWARD ||
+                   !multi2d_tile_ok(p->r, p->prob.dtype == SW_F64 ? 8 : 4, tile, extent)) {
+            return fail(SW_ERR_UNSUPPORTED, "no such tile and step count for this plan and role");
+        }
+    }
+    p->pin[role].tile = std::max(-1, tile);
+    p->pin[role].extent = extent;
+    if (p->graph_exec) {
+        (void)hipGraphExecDestroy(static_cast<hipGraphExec_t>(p->graph_exec));
+        p->graph_exec = nullptr;
+    }
+    return SW_OK;
+}
+
+sw_status sw_plan_get_launch(const sw_plan *p, int32_t role, sw_launch *out)
+{
+    set_error("");
+    if (!p || !out) return fail(SW_ERR_ARG, "NULL argument");
+    if (role < 0 || role > 3) return fail(SW_ERR_ARG, "unknown role");
+    if (const Multi2DChoice c = multi2d_choice(p); c.steps && role == SW_ROLE_FORWARD) {
+        const int vb = p->prob.dtype == SW_F64 ? 8 : 4;
+        const Multi2DTile t = multi2d_tile(c.tile, vb);
+        *out = sw_launch{SW_TILES_STEPS, c.tile, t.ez - 2 * p->r * c.steps,
+                         t.ey - 2 * multi2d_pad_y(p->r * c.steps, vb), 0, c.steps};
+        return SW_OK;
+    }
+    const VecChoice v = choose_vec(p, role);
+    *out = sw_launch{SW_TILES_VECTOR, v.tile, 0, 0, v.zc, 1};
+    if (v.tile >= 0) {
+        vec_extents(p, v.tile, out->rows, out->cols);
+        return SW_OK;
+    }
+    const Tiling t = role == SW_ROLE_FORWARD ? choose_tiling(p) : mode_tiling(p, role);
+    StencilParams P{};
+    set_tiles(p, t, P);
+    *out = sw_launch{SW_TILES_BLOCK, -1, t.tx, tile_cols(p, t.ts), P.zc, t.ts};
     return SW_OK;
 }
 

@@ -14,7 +14,6 @@
 
 #include "device64.h"
 #include "forward2d.h"
-#include "multi2d.h"
 #include "runtime.h"
 
 namespace sw {
@@ -27,15 +26,6 @@ constexpr int64_t kAlign = 256;
 int64_t align_up(int64_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 int value_bytes(const sw_plan *p) { return p->prob.dtype == SW_F64 ? 8 : 4; }
-
-Multi2DChoice choice_of(const sw_plan *p)
-{
-    Multi2DChoice c{};
-    if (p->ndim != 2 || p->prob.scheme != SW_CONST || p->src.unode.size() > size_t(kMaxInjected) ||
-        p->field_elems > std::numeric_limits<int32_t>::max())   // 32-bit element offsets
-        return c;
-    return choose_multi2d(p->r, value_bytes(p), p->dims[0], p->dims[2]);
-}
 
 // Byte offsets in the scratch: buffer k (0, 1: the second pair; from 2 on the
 // levels between, T - 2 of them per set), then the injected values.
@@ -80,16 +70,25 @@ int pow2_group(int n)
 
 }  // namespace
 
+Multi2DChoice multi2d_choice(const sw_plan *p)
+{
+    if (p->ndim != 2 || p->prob.scheme != SW_CONST || p->src.unode.size() > size_t(kMaxInjected) ||
+        p->field_elems > std::numeric_limits<int32_t>::max())   // 32-bit element offsets
+        return {};
+    if (p->pin[0].tile >= 0) return {p->pin[0].extent, p->pin[0].tile};
+    return choose_multi2d(p->r, value_bytes(p), p->dims[0], p->dims[2]);
+}
+
 int64_t multi2d_scratch_bytes(const sw_plan *p)
 {
-    const Multi2DChoice c = choice_of(p);
+    const Multi2DChoice c = multi2d_choice(p);
     return c.steps ? ScratchMap(p, c.steps).total : 0;
 }
 
 template <typename T>
 int multi2d_singles(const sw_plan *p, const Run2D<T> &io, const void *scratch, int64_t bytes)
 {
-    const Multi2DChoice c = choice_of(p);
+    const Multi2DChoice c = multi2d_choice(p);
     if (!c.steps || !scratch || bytes < ScratchMap(p, c.steps).total) return -1;
     // checkpoints of a plan with mirror sides hold the ghosts that the
     // single-step kernels leave in the halo
@@ -106,7 +105,7 @@ template <typename T>
 sw_status enqueue_multi2d(const sw_plan *p, const Run2D<T> &io, int singles, void *scratch, hipStream_t s)
 {
     constexpr bool f64 = std::is_same_v<T, double>;
-    const Multi2DChoice choice = choice_of(p);
+    const Multi2DChoice choice = multi2d_choice(p);
     const Multi2DTile tile = multi2d_tile(choice.tile, int(sizeof(T)));
     const ScratchMap map(p, choice.steps);
     char *base = static_cast<char *>(scratch);

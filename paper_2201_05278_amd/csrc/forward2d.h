@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "multi2d.h"
 #include "plan.h"
 
 namespace sw {
@@ -18,6 +19,9 @@ struct Run2D {
     T *traces, *snaps, *ckpt;
     int saving_stride, ckpt_every, step0, nsteps_run;
 };
+
+// Tile and steps per launch of the plan (steps 0: the single-step kernels).
+Multi2DChoice multi2d_choice(const sw_plan *p);
 
 // Scratch bytes of a run of the plan's steps (0: the plan takes the single-step kernels).
 int64_t multi2d_scratch_bytes(const sw_plan *p);

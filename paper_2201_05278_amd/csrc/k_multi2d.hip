@@ -365,11 +365,10 @@ Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y)
     Multi2DChoice best{};
     double cost = (8.5 + 1.75 * r + 1e-6 * value_bytes * double(Z) * Y) / 1.25;
     for (int tile = 0; tile < int(sizeof(kTiles) / sizeof(kTiles[0])); ++tile) {
-        if (tile == 0 && r > (value_bytes == 4 ? kWideMax<float> : kWideMax<double>)) continue;
         const Multi2DTile t = multi2d_tile(tile, value_bytes);
         for (int nt = 2; nt <= kMulti2DMax; ++nt) {
             const int tz = t.ez - 2 * r * nt, ty = t.ey - 2 * multi2d_pad_y(r * nt, value_bytes);
-            if (tz < 1 || ty < 1) break;
+            if (!multi2d_tile_ok(r, value_bytes, tile, nt)) break;
             const double tiles = double((Z + tz - 1) / tz) * ((Y + ty - 1) / ty);
             const double per_cu = std::ceil(tiles / kCUs);
             int rows = 0;
@@ -384,6 +383,15 @@ Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y)
         }
     }
     return best;
+}
+
+bool multi2d_tile_ok(int r, int value_bytes, int tile, int steps)
+{
+    if (tile < 0 || tile >= int(sizeof(kTiles) / sizeof(kTiles[0])) || steps < 2 || steps > kMulti2DMax ||
+        (tile == 0 && r > (value_bytes == 4 ? kWideMax<float> : kWideMax<double>)))
+        return false;
+    const Multi2DTile t = multi2d_tile(tile, value_bytes);
+    return t.ez > 2 * r * steps && t.ey > 2 * multi2d_pad_y(r * steps, value_bytes);
 }
 
 Multi2DTile multi2d_tile(int tile, int value_bytes)

@@ -51,6 +51,8 @@ struct Multi2DChoice {
 };
 Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y);
 Multi2DTile multi2d_tile(int tile, int value_bytes);
+// Whether a tile is instantiated at a radius and holds any output after `steps` steps.
+bool multi2d_tile_ok(int r, int value_bytes, int tile, int steps);
 // Columns around a tile's outputs: nt R rounded up to whole 16-byte vectors.
 constexpr int multi2d_pad_y(int halo, int value_bytes)
 {

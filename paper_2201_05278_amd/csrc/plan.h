@@ -96,6 +96,11 @@ struct sw_plan {
     // stencil tiling chosen by sw_plan_set_tiling / sw_plan_autotune (tx == 0: default)
     int tile_tx = 0, tile_nw = 0, tile_zc = 0, tile_nt = -1, tile_pf = 0, tile_wt = 0, tile_ts = 0,
         tile_occ = -1, tile_order = 0;
+    // vector or multi-step tile per role (forward, recompute, image, image pair)
+    // set by sw_plan_set_launch, with its z chunk or steps per launch (tile -1: the library's choice)
+    struct Pin {
+        int tile = -1, extent = 0;
+    } pin[4];
     // bumped by every call that changes what a captured launch bakes in
     // (point tables and counts, model, tiling); part of the graph keys
     uint64_t generation = 1;

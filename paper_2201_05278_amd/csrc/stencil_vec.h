@@ -389,14 +389,11 @@ constexpr auto vec_kernel()
     else return k_vec<T, R, TX, LPR, MODE, 1>;
 }
 
-// Tiles of a value type and mode: index I of kVecTiles, or none where the
-// block's threads leave too few registers (768 threads: 168 each; 1024: 128).
+// Tiles of a value type and mode: index I of kVecTiles.
 template <typename T, int R, int MODE, int I>
 constexpr bool vec_has()
 {
-    constexpr int threads = kVecTiles<T>[I].tx * kVecTiles<T>[I].lpr;
-    constexpr int need = 76 + 9 * R + (MODE == MODE_IMAGE ? 16 : MODE == MODE_IMAGE2 ? 26 : 0);
-    return threads <= 512 || (threads <= 768 && need <= 160);
+    return vec_fits(kVecTiles<T>[I].tx * kVecTiles<T>[I].lpr, R, MODE);
 }
 
 template <typename T, int R, int MODE, int I>

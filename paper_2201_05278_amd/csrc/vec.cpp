@@ -149,10 +149,9 @@ VecChoice choose(const sw_plan *p, int mode)
     const int slots = resident<T>(p->r, kFourWaves, mode);  // waves per SIMD
     if (slots <= 0) return best;
     const int Z = p->dims[0], X = p->dims[1], Y = p->dims[2], R = p->r;
-    const int64_t pbytes = int64_t(p->pad[1]) * p->pad[2] * int64_t(sizeof(T));
     const bool edges = p->prob.bc[1][0] || p->prob.bc[1][1] || p->prob.bc[2][0] || p->prob.bc[2][1];
     const bool image = mode == MODE_IMAGE || mode == MODE_IMAGE2;
-    const int zmax = int(std::max<int64_t>(1, (int64_t(1) << 31) / pbytes - 4 * R - 2));
+    const int zmax = vec_zmax(p);
     double cost = 0.0;
     for (int i = 0; i < kVecTileCount; ++i) {
         const VecTile t = kVecTiles<T>[i];
@@ -206,8 +205,7 @@ VecChoice choose_vd(const sw_plan *p)
     const VdCost m = stag ? kStagCost : kCentCost;
     const int Z = p->dims[0], X = p->dims[1], Y = p->dims[2], R = p->r;
     const int warm = stag ? 2 * R - 1 : 2 * R;
-    const int64_t pbytes = int64_t(p->pad[1]) * p->pad[2] * 4;
-    const int zmax = int(std::max<int64_t>(1, (int64_t(1) << 31) / pbytes - 4 * R - 2));
+    const int zmax = vec_zmax(p);
     double cost = 0.0;
     for (int i = 0; i < kVdTileCount; ++i) {
         const VdTile t = kVdTiles[i];
@@ -259,9 +257,42 @@ bool vd_vectors(const sw_plan *p, int mode)
 
 }  // namespace
 
+int vec_zmax(const sw_plan *p)
+{
+    const int64_t pbytes = int64_t(p->pad[1]) * p->pad[2] * (p->prob.dtype == SW_F64 ? 8 : 4);
+    return int(std::max<int64_t>(1, (int64_t(1) << 31) / pbytes - 4 * p->r - 2));
+}
+
+bool vec_instance(const sw_plan *p, int mode, int tile)
+{
+    const bool f64 = p->prob.dtype == SW_F64, vd = p->prob.scheme != SW_CONST;
+    if (p->ndim != 3 || tile < 0 || tile >= (vd ? kVdTileCount : kVecTileCount)) return false;
+    if (mode != MODE_FWD && (p->mirror || f64 || p->prob.scheme == SW_VD_CENTRED)) return false;
+    if (vd) {
+        if (p->prob.scheme == SW_VD_STAGGERED && (p->r < kStagRadii[0] || p->r > kStagRadii[1])) return false;
+        return kVdTiles[tile].tx * kVdTiles[tile].ty / vd_columns(p->prob.scheme, p->r) <= kVdThreads;
+    }
+    const VecTile t = f64 ? kVecTiles<double>[tile] : kVecTiles<float>[tile];
+    return vec_fits(t.tx * t.lpr, p->r, mode);
+}
+
+void vec_extents(const sw_plan *p, int tile, int &rows, int &cols)
+{
+    const bool f64 = p->prob.dtype == SW_F64;
+    if (p->prob.scheme != SW_CONST) {
+        rows = kVdTiles[tile].tx;
+        cols = kVdTiles[tile].ty;
+    } else {
+        rows = f64 ? kVecTiles<double>[tile].tx : kVecTiles<float>[tile].tx;
+        cols = f64 ? kVecTiles<double>[tile].lpr * 2 : kVecTiles<float>[tile].lpr * 4;
+    }
+}
+
 VecChoice choose_vec(const sw_plan *p, int mode)
 {
     if (p->ndim != 3 || !default_tiling(p) || (p->mirror && mode != MODE_FWD)) return {};
+    if (const sw_plan::Pin &pin = p->pin[mode]; pin.tile >= 0)
+        return {pin.tile, std::min(pin.extent, p->dims[0]), p->prob.scheme == SW_CONST && p->mirror};
     if (p->prob.scheme != SW_CONST) return vd_vectors(p, mode) ? choose_vd(p) : VecChoice{};
     if (p->mirror) mode = kVecMirror;
     VecChoice c = p->prob.dtype == SW_F64 ? choose<double>(p, mode) : choose<float>(p, mode);

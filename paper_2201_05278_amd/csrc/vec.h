@@ -29,6 +29,20 @@ struct VecChoice {
 // Tile and chunk of a 3D plan with default tiling in a mode.
 VecChoice choose_vec(const sw_plan *p, int mode);
 
+// Whether the plan's launches in a mode have vector tile `tile`, and the longest z chunk of its 32-bit windows.
+bool vec_instance(const sw_plan *p, int mode, int tile);
+int vec_zmax(const sw_plan *p);
+// Rows and columns of a vector tile of the plan.
+void vec_extents(const sw_plan *p, int tile, int &rows, int &cols);
+
+// Threads and mode of a kernel for which a block's registers suffice (768
+// threads: 168 each; 1024: 128).
+constexpr bool vec_fits(int threads, int r, int mode)
+{
+    const int need = 76 + 9 * r + (mode == MODE_IMAGE ? 16 : mode == MODE_IMAGE2 ? 26 : 0);
+    return threads <= 512 || (threads <= 768 && need <= 160);
+}
+
 // Launch with a choice: sets the tile counts of P.
 template <typename T>
 hipError_t launch_vec(int r, const VecChoice &c, int mode, StencilParamsT<T> &P, hipStream_t s);

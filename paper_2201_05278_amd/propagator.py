@@ -292,6 +292,21 @@ class Propagator:
         L.check("sw_plan_get_tiling", L.lib().sw_plan_get_tiling(self._plan, ctypes.byref(t)))
         return {k: getattr(t, k) for k, _ in L.Tiling._fields_}
 
+    def launch(self, role="forward"):
+        """What the stencil launches run in a role (forward, recompute, image or
+        image_pair): the kind of tile (block, vector or steps), its index and
+        extents, the z chunk and the time steps per launch."""
+        t = L.Launch()
+        L.check("sw_plan_get_launch", L.lib().sw_plan_get_launch(self._plan, L.ROLES[role], ctypes.byref(t)))
+        out = {k: getattr(t, k) for k, _ in L.Launch._fields_}
+        out["kind"] = L.TILE_KINDS[t.kind]
+        return out
+
+    def set_launch(self, tile=-1, extent=0, role="forward"):
+        """Vector tile and z chunk of a role (3D), or multi-step tile and steps per
+        launch (2D); tile -1: the library's choice."""
+        L.check("sw_plan_set_launch", L.lib().sw_plan_set_launch(self._plan, L.ROLES[role], int(tile), int(extent)))
+
     @property
     def occupancy(self):
         """(resident blocks per CU, CUs) of the stencil kernel under the current

@@ -1,0 +1,158 @@
+"""Every vector and multi-step tile, chosen by hand on small ragged grids, bitwise against the scalar single-step kernels
+(which the oracle tests pin); and the kernels that the library chooses by itself."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2201_05278_amd import Propagator, SimwaveError, critical_dt, ricker
+from paper_2201_05278_amd import _lib as L
+
+pytestmark = pytest.mark.gpu
+
+ODD = (("dirichlet", "neumann"), ("neumann", "dirichlet"), ("none", "neumann"))
+H = (10.0, 12.0, 9.0)
+
+
+def _prop(n, so, steps, nbl=0, scheme="const", dtype="float32", bc=None):
+    h = H[:len(n)]
+    dt = 0.5 * critical_dt(h, so, 3000.0)
+    prop = Propagator(n, h, so, dt, steps, scheme=scheme, nbl=nbl, bc=bc, dtype=dtype)
+    mid = [hh * (k - 1) / 2 for k, hh in zip(n, h)]
+    prop.set_sources([mid], "linear")
+    prop.set_receivers([mid, [0.9 * m for m in mid]], "linear")
+    rng = np.random.default_rng(so)
+    vel = torch.from_numpy(rng.uniform(1500.0, 3000.0, n)).to(prop.torch_dtype)
+    rho = None if scheme == "const" else torch.from_numpy(rng.uniform(1000.0, 2500.0, n)).float()
+    prop.prepare(vel, rho, cmax=3000.0)
+    return prop, ricker(30.0, dt, steps).reshape(-1, 1).cuda()
+
+
+def _run(prop, wav, steps=None):
+    """Traces and both levels of a run (of `steps` steps) that resumes from noise on the whole grid."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    fields = []
+    for _ in range(2):
+        f = prop.new_field()
+        v = prop.grid_view(f)
+        v.copy_(torch.randn(tuple(v.shape), generator=g, device="cuda", dtype=v.dtype))
+        fields.append(f)
+    res = prop.forward(wav, fields=tuple(fields), step0=1, nsteps_run=steps or prop.nsteps - 1)
+    return [res.traces] + [prop.grid_view(f) for f in fields]
+
+
+def _tiles(prop, extent, roles=("forward",), count=8):
+    """Sets each tile that every one of the roles has, in turn."""
+    for tile in range(count):
+        try:
+            for role in roles:
+                prop.set_launch(tile, extent, role)
+        except SimwaveError as e:
+            assert L.STATUS[e.status] == "SW_ERR_UNSUPPORTED"
+            continue
+        for role in roles:
+            assert (prop.launch(role)["kind"], prop.launch(role)["tile"], prop.launch(role)["zc"]) == ("vector", tile, extent)
+        yield tile
+
+
+def _same(a, b):
+    assert len(a) == len(b) and float(b[-1].abs().max()) > 0.0
+    return all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("so", range(2, 21, 2))
+@pytest.mark.parametrize("scheme,dtype", [("const", "float32"), ("const", "float64"), ("vd_staggered", "float32"),
+                                          ("vd_centred", "float32")])
+def test_every_vector_tile_is_bitwise_the_scalar_tiles(scheme, dtype, so):
+    if scheme == "vd_staggered" and so in (2, 18, 20):
+        pytest.skip("the staggered scheme has vector tiles from SO4 to SO16")
+    # more than two tiles of any extent along x and y, ends inside a vector, uneven chunks
+    for bc, n, nbl in ((None, (25, 40, 131), ((2, 0), (9, 4), (5, 7))), (ODD, (27, 45, 133), ((0, 3), (0, 8), (6, 0)))):
+        prop, wav = _prop(n, so, 6, nbl, scheme, dtype, bc)
+        prop.set_tiling(8, 8)
+        ref = _run(prop, wav)
+        prop.set_tiling()
+        seen = []
+        for tile in _tiles(prop, 10):
+            print(f"case: {scheme} {dtype} SO{so} vector tile {tile} mirror sides {bc is not None}", flush=True)
+            assert _same(_run(prop, wav), ref), (tile, bc)
+            seen.append(tile)
+        assert len(seen) >= 3
+
+
+@pytest.mark.parametrize("so", range(2, 21, 2))
+@pytest.mark.parametrize("scheme", ["const", "vd_staggered"])
+def test_every_vector_tile_of_a_gradient_is_bitwise_the_scalar_tiles(scheme, so):
+    if scheme == "vd_staggered" and so in (2, 18, 20):
+        pytest.skip("the staggered scheme has vector tiles from SO4 to SO16")
+    prop, wav = _prop((25, 40, 131), so, 9, ((2, 0), (9, 4), (5, 7)), scheme)
+    roles, every = ("recompute", "image", "image_pair"), 4           # segments of 4, 4 and 1 steps
+
+    def gradient():
+        fw = prop.forward(wav, checkpoint_every=every)
+        out = prop.adjoint(wav, fw.traces, fw.ckpt, every)
+        return [out[0].clone()] + ([out[3].clone()] if scheme != "const" else [])
+
+    prop.set_tiling(8, 8)
+    ref = gradient()
+    prop.set_tiling()
+    seen = []
+    for tile in _tiles(prop, 10, roles):
+        print(f"case: gradient {scheme} SO{so} vector tile {tile}", flush=True)
+        assert _same(gradient(), ref), tile
+        seen.append(tile)
+    assert len(seen) >= 3
+
+
+@pytest.mark.parametrize("so", range(2, 21, 2))
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_every_2d_tile_and_step_count_is_bitwise_single_steps(monkeypatch, dtype, so):
+    for bc, n, nbl in ((None, (75, 130), ((3, 9), (11, 2))), (ODD[:2], (73, 131), ((0, 7), (0, 0)))):
+        prop, wav = _prop(n, so, 18, nbl, "const", dtype, bc)
+        with monkeypatch.context() as m:
+            m.setattr(prop, "_scratch", lambda graph: None)
+            ref = {k: _run(prop, wav, 2 * k) for k in range(2, 9)}
+        seen = []
+        for tile in range(5):
+            for steps in range(2, 9):
+                try:
+                    prop.set_launch(tile, steps)
+                except SimwaveError as e:
+                    assert L.STATUS[e.status] == "SW_ERR_UNSUPPORTED"
+                    continue
+                assert (prop.launch()["kind"], prop.launch()["tile"], prop.launch()["steps"]) == ("steps", tile, steps)
+                print(f"case: 2D {dtype} SO{so} tile {tile}, {steps} steps per launch, mirror sides {bc is not None}", flush=True)
+                assert _same(_run(prop, wav, 2 * steps), ref[steps]), (tile, steps, bc)     # two launches of `steps`
+                seen.append(steps)
+        assert seen or so > (20 if dtype == "float32" else 14)
+
+
+@pytest.mark.parametrize("n,so,scheme,dtype,bc,kind", [
+    ((60, 70, 80), 2, "const", "float32", None, "vector"),
+    ((9, 7, 5), 8, "const", "float32", None, "vector"),
+    ((1, 40, 40), 4, "const", "float32", None, "vector"),
+    ((200, 130, 257), 8, "const", "float32", None, "vector"),
+    ((150, 160, 170), 6, "const", "float32", ODD, "vector"),
+    ((70, 44, 58), 20, "const", "float32", ODD, "vector"),
+    ((60, 71, 83), 2, "const", "float64", ODD, "vector"),
+    ((38, 41, 59), 20, "const", "float64", None, "vector"),
+    ((60, 70, 80), 2, "vd_staggered", "float32", None, "block"),
+    ((45, 33, 61), 4, "vd_staggered", "float32", ODD, "vector"),
+    ((200, 130, 257), 8, "vd_staggered", "float32", None, "vector"),
+    ((60, 50, 90), 16, "vd_staggered", "float32", None, "vector"),
+    ((70, 44, 58), 20, "vd_staggered", "float32", None, "block"),
+    ((60, 70, 80), 2, "vd_centred", "float32", None, "vector"),
+    ((60, 50, 90), 16, "vd_centred", "float32", ODD, "vector"),
+    ((70, 44, 58), 20, "vd_centred", "float32", None, "vector"),
+    ((97, 130), 4, "const", "float32", None, "steps"),
+    ((44, 70), 20, "const", "float32", ODD[:2], "steps"),
+    ((90, 47), 12, "const", "float64", None, "steps"),
+    ((90, 47), 16, "const", "float64", None, "block"),
+    ((97, 130), 8, "vd_staggered", "float32", None, "block"),
+])
+def test_kernels_that_the_library_chooses(n, so, scheme, dtype, bc, kind):
+    prop, _ = _prop(n, so, 5, 4, scheme, dtype, bc)
+    assert prop.launch()["kind"] == kind
+    gradient = dtype == "float32" and bc is None and scheme != "vd_centred" and len(n) == 3
+    for role in ("recompute", "image", "image_pair") if gradient else ():
+        assert prop.launch(role)["kind"] == kind

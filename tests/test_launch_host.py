@@ -1,0 +1,71 @@
+"""Which kernels a plan can be made to launch (no GPU)."""
+import pytest
+
+from paper_2201_05278_amd import Propagator, SimwaveError
+from paper_2201_05278_amd import _lib as L
+
+
+def _plan(n, so, scheme="const", dtype="float32", bc=None):
+    return Propagator(n, (10.0,) * len(n), so, 1e-4, 20, scheme=scheme, nbl=4, device="cpu", dtype=dtype, bc=bc)
+
+
+def _tiles(prop, role="forward", extent=7, count=10):
+    """Indices that set_launch accepts."""
+    out = []
+    for tile in range(count):
+        try:
+            prop.set_launch(tile, extent, role)
+            out.append(tile)
+            assert (prop.launch(role)["tile"], prop.launch(role)["kind"]) == (tile, "vector")
+        except SimwaveError as e:
+            assert L.STATUS[e.status] == "SW_ERR_UNSUPPORTED"
+    return out
+
+
+def test_vector_tiles_of_every_scheme_and_role():
+    n, free = (40, 44, 48), (("none", "neumann"),) * 3
+    assert _tiles(_plan(n, 8)) == list(range(8))
+    assert _tiles(_plan(n, 20)) == list(range(7))               # 768 threads with 166 registers each
+    assert _tiles(_plan(n, 14), "image_pair") == list(range(7))
+    assert _tiles(_plan(n, 8, bc=free)) == list(range(8)) and _tiles(_plan(n, 8, bc=free), "recompute") == []
+    assert _tiles(_plan(n, 8, dtype="float64")) == list(range(8)) and _tiles(_plan(n, 8, dtype="float64"), "image") == []
+    assert _tiles(_plan(n, 8, "vd_staggered")) == [0, 1, 2, 3, 4]
+    assert _tiles(_plan(n, 16, "vd_staggered"), "image") == [0, 1, 3]   # two columns per thread
+    assert _tiles(_plan(n, 2, "vd_staggered")) == [] and _tiles(_plan(n, 18, "vd_staggered")) == []
+    assert _tiles(_plan(n, 20, "vd_centred")) == [0, 1, 3] and _tiles(_plan(n, 8, "vd_centred"), "recompute") == []
+
+
+def test_a_launch_is_refused_or_taken_back():
+    prop = _plan((40, 44, 48), 8)
+    own = prop.launch()
+    for bad in ((0, 0), (0, 1 << 20), (0, -3)):
+        with pytest.raises(SimwaveError, match="z chunk"):
+            prop.set_launch(*bad)
+    prop.set_launch(3, 9)
+    assert prop.launch() == {"kind": "vector", "tile": 3, "rows": 24, "cols": 64, "zc": 9, "steps": 1}
+    assert prop.launch("image")["tile"] != 3 or prop.launch("image")["zc"] != 9
+    prop.set_launch()
+    assert prop.launch() == own
+    prop.set_launch(3, 9)
+    prop.set_tiling(8, 8)
+    assert prop.launch()["kind"] == "block" and (prop.launch()["rows"], prop.launch()["cols"]) == (8, 64)
+    with pytest.raises(SimwaveError, match="tiling of its own"):
+        prop.set_launch(3, 9)
+    prop.set_tiling()
+    assert prop.launch() == own
+
+
+def test_steps_per_launch_in_2d():
+    prop = _plan((60, 80), 8)
+    own = prop.launch()
+    assert own["kind"] == "steps" and own["steps"] >= 2
+    prop.set_launch(1, 3)
+    assert prop.launch() == {"kind": "steps", "tile": 1, "rows": 8, "cols": 104, "zc": 0, "steps": 3}
+    for bad in ((1, 4), (1, 1), (0, 9), (5, 2)):                # 32 rows hold no output after 4 steps
+        with pytest.raises(SimwaveError, match="no such tile"):
+            prop.set_launch(*bad)
+    prop.set_launch()
+    assert prop.launch() == own
+    with pytest.raises(SimwaveError, match="no such tile"):
+        _plan((60, 80), 8, "vd_staggered").set_launch(1, 3)
+    assert _plan((60, 80), 8, "vd_staggered").launch()["kind"] == "block"
