@@ -886,8 +886,8 @@ static sw_status enqueue_forward(sw_plan *p, const sw_fwd_io *io, void *scratch,
             continue;
         }
         SW_HIP(checkpoint(n, cur, nxt));
-        // the constant-density vector tiles make mirror ghosts themselves (checkpoints keep those of the fill)
-        if (p->mirror && (vec.tile < 0 || p->prob.scheme != SW_CONST || io->ckpt)) SW_HIP(launch_ghost_fill(g, p->bcm, p->ghost, cur, s));
+        if (fills_ghosts(p, vec) || (p->mirror && io->ckpt))     // (checkpoints hold the ghosts of the fill)
+            SW_HIP(launch_ghost_fill(g, p->bcm, p->ghost, cur, s));
         P.cur = cur;
         P.nxt = nxt;
         if (!ev.empty()) SW_HIP(hipEventRecord(ev[2 * k], s));

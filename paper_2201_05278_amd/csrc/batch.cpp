@@ -471,8 +471,10 @@ sw_status sw_plan_autotune(sw_plan *p, const sw_fwd_io *io, const char *cache_pa
         st = sw_plan_set_tiling(p, &cand);
         if (st != SW_OK) continue;
         const VecChoice vec = choose_vec(p, MODE_FWD);
-        // per-step time: single sweeps, or two-step sweeps over half as many launches
+        // per-step time: single sweeps with the ghost fill that they need, or two-step sweeps over half as many launches
         auto run = [&]() -> hipError_t {
+            if (fills_ghosts(p, vec))
+                if (const hipError_t e = launch_ghost_fill(P.g, p->bcm, p->ghost, io->field[0], s); e != hipSuccess) return e;
             if (cand.ts == 2)
                 return stencil_two(p, io, 0, io->field[0], io->field[1], io->field2[0], io->field2[1], false, s);
             return stencil(p, MODE_FWD, P, vec, s);

@@ -34,6 +34,12 @@ Tiling choose_tiling(const sw_plan *p);
 bool default_tiling(const sw_plan *p);
 void fill_params(const sw_plan *p, void *ws, StencilParams &P);
 void set_tiles(const sw_plan *p, const Tiling &t, StencilParams &P);
+// Whether a forward step with that choice reads mirror ghosts from the stored
+// halo (the constant-density vector tiles make them themselves).
+inline bool fills_ghosts(const sw_plan *p, const VecChoice &vec)
+{
+    return p->mirror && (vec.tile < 0 || p->prob.scheme != SW_CONST);
+}
 // One stencil launch; vec: choose_vec's answer for the mode, asked once per run.
 hipError_t stencil(const sw_plan *p, int mode, StencilParams &P, const VecChoice &vec, hipStream_t s);
 bool tb_shape_ok(int r, int tx, int nw);

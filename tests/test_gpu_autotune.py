@@ -1,0 +1,44 @@
+"""What the autotuner times and keeps."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2201_05278_amd import Propagator, critical_dt
+from paper_2201_05278_amd import _lib as L
+
+pytestmark = pytest.mark.gpu
+
+FREE = (("neumann", "dirichlet"), ("none", "none"), ("none", "none"))
+
+
+def _prop(n, so, scheme="const", bc=None):
+    h = (10.0,) * len(n)
+    prop = Propagator(n, h, so, 0.5 * critical_dt(h, so, 3000.0), 20, scheme=scheme, nbl=0, bc=bc)
+    rng = np.random.default_rng(0)
+    vel = torch.from_numpy(rng.uniform(1500.0, 3000.0, n)).float()
+    prop.prepare(vel, None if scheme == "const" else 0.5 * vel, cmax=3000.0)
+    return prop
+
+
+def test_candidates_on_mirror_sides_pay_for_their_ghosts():
+    """The tiles that read stored ghosts are timed with the fill that every one of their steps needs: after the call the ghosts
+    of the level they read are there."""
+    print("case: autotune with mirror sides along z", flush=True)
+    prop = _prop((40, 36, 48), 4, bc=FREE)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    fields = [prop.new_field() for _ in range(2)]
+    grid = prop.grid_view(fields[0])
+    grid.copy_(torch.randn(tuple(grid.shape), generator=g, device="cuda"))
+    io = L.FwdIO()
+    io.workspace = prop.workspace.data_ptr()
+    io.field[0], io.field[1] = fields[0].data_ptr(), fields[1].data_ptr()
+    L.check("sw_plan_autotune", L.lib().sw_plan_autotune(prop._plan, ctypes.byref(io), None, None))
+    torch.cuda.synchronize()
+    lay = prop.layout
+    plane = lay.padded[1] * lay.padded[2]
+    planes = fields[0].as_strided((40 + 4, 36, 48), (plane, lay.padded[2], 1), lay.origin - 2 * plane)
+    assert torch.equal(planes[1], grid[1]) and torch.equal(planes[0], grid[2])          # Neumann: even
+    assert torch.equal(planes[42], -grid[38]) and torch.equal(planes[43], -grid[37])    # Dirichlet: odd
