@@ -465,7 +465,9 @@ sw_status sw_batch_forward_static(sw_batch *batch, const sw_batch_io *io, void *
  * batches) the launch grid (one block per tile or a looping grid), by timing a few steps of each
  * candidate on the given buffers (their contents are overwritten), or reuse
  * the choice stored under the same problem key in the JSON file `cache_path`
- * (may be NULL: no cache).  The choice is kept in the plan / batch and
+ * (may be NULL: no cache).  Candidates of a plan are timed as forward steps: its
+ * choice holds for those (also in the adjoint), while recompute and imaging
+ * launches stay the library's.  The choice is kept in the plan / batch and
  * written back to the cache.  Synchronises `stream`. */
 sw_status sw_plan_autotune(sw_plan *plan, const sw_fwd_io *io, const char *cache_path, void *stream);
 sw_status sw_batch_autotune(sw_batch *batch, const sw_batch_io *io, const char *cache_path,

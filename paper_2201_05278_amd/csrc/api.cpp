@@ -270,9 +270,15 @@ Tiling choose_tiling(const sw_plan *p)
     return t;
 }
 
-// No choice of the caller's or of the autotuner's: the library picks.
-bool default_tiling(const sw_plan *p)
+// Whether the library picks what runs in a mode: no tiling was set, or the
+// autotuner's, which timed forward steps and so leaves the recompute and imaging
+// launches to the library (gradients whose forward steps run scalar tiles, with
+// these launches on the same against vector tiles, 300^3 and 36 steps, ms: SO4
+// 12.5 and 12.4, SO8 14.0 and 13.5, SO16 19.4 and 16.8; staggered SO4 25.2 and
+// 25.5, SO8 33.4 and 32.3, SO12 55.9 and 56.4, SO16 79.1 and 66.7).
+bool library_picks(const sw_plan *p, int mode)
 {
+    if (p->tile_tuned && mode != MODE_FWD) return true;
     return !p->tile_tx && !p->tile_zc && p->tile_nt < 0 && !p->tile_pf && p->tile_ts != 2 && p->tile_occ < 0 && !p->tile_order;
 }
 
@@ -596,6 +602,7 @@ sw_status sw_plan_set_tiling(sw_plan *p, const sw_tiling *t)
     p->tile_ts = d.ts;
     p->tile_occ = d.occ;
     p->tile_order = d.order;
+    p->tile_tuned = false;
     for (auto &pin : p->pin) pin = {};
     if (p->graph_exec) {
         (void)hipGraphExecDestroy(static_cast<hipGraphExec_t>(p->graph_exec));
@@ -610,7 +617,7 @@ sw_status sw_plan_set_launch(sw_plan *p, int32_t role, int32_t tile, int32_t ext
     if (!p) return fail(SW_ERR_ARG, "plan is NULL");
     if (role < 0 || role > 3) return fail(SW_ERR_ARG, "unknown role");
     if (tile >= 0) {
-        if (!default_tiling(p)) return fail(SW_ERR_STATE, "the plan has a tiling of its own (sw_plan_set_tiling)");
+        if (!library_picks(p, role)) return fail(SW_ERR_STATE, "the plan has a tiling of its own (sw_plan_set_tiling)");
         if (p->ndim == 3) {
             if (!vec_instance(p, role, tile)) return fail(SW_ERR_UNSUPPORTED, "no such vector tile for this plan and role");
             if (extent < 1 || extent > vec_zmax(p)) return fail(SW_ERR_ARG, "z chunk outside 1 .. the longest window");

@@ -421,7 +421,10 @@ sw_status sw_plan_autotune(sw_plan *p, const sw_fwd_io *io, const char *cache_pa
         auto &v = it->second;
         const sw_tiling t{v["tx"], v["nw"], v["zc"], v["nt"], v["pf"], v["wt"], v["ts"],
                           v.count("occ") ? v["occ"] : -1, v.count("order") ? v["order"] : 0};
-        if (sw_plan_set_tiling(p, &t) == SW_OK) return SW_OK;
+        if (sw_plan_set_tiling(p, &t) == SW_OK) {
+            p->tile_tuned = true;
+            return SW_OK;
+        }
         // a cached choice this plan rejects (a stale or hand-edited entry): tune again
         set_error("");
     }
@@ -495,6 +498,7 @@ sw_status sw_plan_autotune(sw_plan *p, const sw_fwd_io *io, const char *cache_pa
     (void)hipEventDestroy(e1);
     st = sw_plan_set_tiling(p, &best_t);
     if (st != SW_OK) return st;
+    p->tile_tuned = true;
     cache[key] = {{"tx", best_t.tx}, {"nw", best_t.nw}, {"zc", best_t.zc}, {"nt", best_t.nt},
                   {"pf", best_t.pf}, {"wt", best_t.wt}, {"ts", best_t.ts}, {"occ", best_t.occ},
                   {"order", best_t.order}};

@@ -96,6 +96,7 @@ struct sw_plan {
     // stencil tiling chosen by sw_plan_set_tiling / sw_plan_autotune (tx == 0: default)
     int tile_tx = 0, tile_nw = 0, tile_zc = 0, tile_nt = -1, tile_pf = 0, tile_wt = 0, tile_ts = 0,
         tile_occ = -1, tile_order = 0;
+    bool tile_tuned = false;        // the tiling is the autotuner's: it holds for the launches that were timed
     // vector or multi-step tile per role (forward, recompute, image, image pair)
     // set by sw_plan_set_launch, with its z chunk or steps per launch (tile -1: the library's choice)
     struct Pin {

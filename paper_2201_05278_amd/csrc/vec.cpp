@@ -290,7 +290,7 @@ void vec_extents(const sw_plan *p, int tile, int &rows, int &cols)
 
 VecChoice choose_vec(const sw_plan *p, int mode)
 {
-    if (p->ndim != 3 || !default_tiling(p) || (p->mirror && mode != MODE_FWD)) return {};
+    if (p->ndim != 3 || !library_picks(p, mode) || (p->mirror && mode != MODE_FWD)) return {};
     if (const sw_plan::Pin &pin = p->pin[mode]; pin.tile >= 0)
         return {pin.tile, std::min(pin.extent, p->dims[0]), p->prob.scheme == SW_CONST && p->mirror};
     if (p->prob.scheme != SW_CONST) return vd_vectors(p, mode) ? choose_vd(p) : VecChoice{};

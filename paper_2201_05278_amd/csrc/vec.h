@@ -26,7 +26,7 @@ struct VecChoice {
     bool mirror = false;        // the plan has mirror sides
 };
 
-// Tile and chunk of a 3D plan with default tiling in a mode.
+// Tile and chunk of a 3D plan in a mode that the library picks for.
 VecChoice choose_vec(const sw_plan *p, int mode);
 
 // Whether the plan's launches in a mode have vector tile `tile`, and the longest z chunk of its 32-bit windows.

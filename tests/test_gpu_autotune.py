@@ -1,5 +1,6 @@
 """What the autotuner times and keeps."""
 import ctypes
+import json
 
 import numpy as np
 import pytest
@@ -42,3 +43,29 @@ def test_candidates_on_mirror_sides_pay_for_their_ghosts():
     planes = fields[0].as_strided((40 + 4, 36, 48), (plane, lay.padded[2], 1), lay.origin - 2 * plane)
     assert torch.equal(planes[1], grid[1]) and torch.equal(planes[0], grid[2])          # Neumann: even
     assert torch.equal(planes[42], -grid[38]) and torch.equal(planes[43], -grid[37])    # Dirichlet: odd
+
+
+def _tuned(prop, cache, **entry):
+    """Autotune with a cache file that holds `entry` for the plan."""
+    prop.autotune(str(cache))
+    text = json.loads(cache.read_text())
+    (key,) = text
+    known = dict(text[key])
+    text[key].update(entry)
+    cache.write_text(json.dumps({key: {k: v for k, v in text[key].items() if v is not None}}))
+    prop.set_tiling()
+    prop.autotune(str(cache))
+    return known, json.loads(cache.read_text())[key]
+
+
+def test_a_tuned_forward_leaves_recompute_and_imaging_to_the_library(tmp_path):
+    print("case: gradient launches of a tuned plan", flush=True)
+    for scheme in ("const", "vd_staggered"):
+        prop = _prop((40, 36, 48), 8, scheme)
+        own = {role: prop.launch(role) for role in ("recompute", "image", "image_pair")}
+        _tuned(prop, tmp_path / scheme, tx=8, nw=8, zc=20, nt=1, pf=1, wt=0, ts=0, occ=-1, order=0)
+        assert (prop.launch()["kind"], prop.launch()["rows"], prop.launch()["zc"]) == ("block", 8, 20)
+        for role, was in own.items():
+            assert was["kind"] == "vector" and prop.launch(role) == was
+        prop.set_tiling(8, 8)                                  # the caller's own choice holds for every role
+        assert all(prop.launch(role)["kind"] == "block" for role in own)
