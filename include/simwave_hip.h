@@ -240,7 +240,7 @@ sw_status sw_forward(sw_plan *plan, const sw_fwd_io *io, void *stream);
 
 /* Device bytes with which sw_forward_scratch / sw_forward_f64_scratch run
  * faster than sw_forward / sw_forward_f64 (0: the plan has no use for any).
- * Depends on the grid, the step count and the sources. */
+ * Depends on the grid, the step count, the sources and the tiling. */
 sw_status sw_plan_scratch(const sw_plan *plan, int64_t *bytes);
 
 /* sw_forward with `scratch_bytes` bytes of caller-owned device memory at
@@ -335,7 +335,8 @@ sw_status sw_adjoint(sw_plan *plan, const sw_adj_io *io, void *stream);
 /* Stencil tiling of a plan.  Results never depend on it.  A 3D plan whose
  * tiling is left at the defaults runs vector tiles where those are faster (16
  * bytes of columns per thread; tile and z chunk from a cost model of the
- * launch); any field set here makes it run the tiles described below.
+ * launch); any field set here makes it run the tiles described below.  A 2D
+ * plan likewise runs single steps, with or without scratch, once a field is set.
  *   tx, nw  rows per block and waves per block.  3D constant density:
  *           block tiles (16,4), (8,4), (32,8), (16,8), (8,8), (24,8), or with wt = 1
  *           wave tiles (16,4), (32,4), (4,1), (8,1), (16,2) (each wave owns
@@ -465,9 +466,9 @@ sw_status sw_batch_forward_static(sw_batch *batch, const sw_batch_io *io, void *
  * batches) the launch grid (one block per tile or a looping grid), by timing a few steps of each
  * candidate on the given buffers (their contents are overwritten), or reuse
  * the choice stored under the same problem key in the JSON file `cache_path`
- * (may be NULL: no cache).  Candidates of a plan are timed as forward steps: its
- * choice holds for those (also in the adjoint), while recompute and imaging
- * launches stay the library's.  The choice is kept in the plan / batch and
+ * (may be NULL: no cache).  Candidates of a plan are timed as single forward steps:
+ * its choice holds for those (also in the adjoint), while recompute and imaging
+ * launches, and 2D launches of several steps, stay the library's.  The choice is kept in the plan / batch and
  * written back to the cache.  Synchronises `stream`. */
 sw_status sw_plan_autotune(sw_plan *plan, const sw_fwd_io *io, const char *cache_path, void *stream);
 sw_status sw_batch_autotune(sw_batch *batch, const sw_batch_io *io, const char *cache_path,

@@ -271,14 +271,14 @@ Tiling choose_tiling(const sw_plan *p)
 }
 
 // Whether the library picks what runs in a mode: no tiling was set, or the
-// autotuner's, which timed forward steps and so leaves the recompute and imaging
-// launches to the library (gradients whose forward steps run scalar tiles, with
+// autotuner's, which timed single forward steps and so leaves the recompute and
+// imaging launches, and 2D launches of several steps, to the library (gradients whose forward steps run scalar tiles, with
 // these launches on the same against vector tiles, 300^3 and 36 steps, ms: SO4
 // 12.5 and 12.4, SO8 14.0 and 13.5, SO16 19.4 and 16.8; staggered SO4 25.2 and
 // 25.5, SO8 33.4 and 32.3, SO12 55.9 and 56.4, SO16 79.1 and 66.7).
 bool library_picks(const sw_plan *p, int mode)
 {
-    if (p->tile_tuned && mode != MODE_FWD) return true;
+    if (p->tile_tuned && (mode != MODE_FWD || p->ndim == 2)) return true;
     return !p->tile_tx && !p->tile_zc && p->tile_nt < 0 && !p->tile_pf && p->tile_ts != 2 && p->tile_occ < 0 && !p->tile_order;
 }
 

@@ -72,7 +72,7 @@ int pow2_group(int n)
 
 Multi2DChoice multi2d_choice(const sw_plan *p)
 {
-    if (p->ndim != 2 || p->prob.scheme != SW_CONST || p->src.unode.size() > size_t(kMaxInjected) ||
+    if (p->ndim != 2 || p->prob.scheme != SW_CONST || !library_picks(p, MODE_FWD) || p->src.unode.size() > size_t(kMaxInjected) ||
         p->field_elems > std::numeric_limits<int32_t>::max())   // 32-bit element offsets
         return {};
     if (p->pin[0].tile >= 0) return {p->pin[0].extent, p->pin[0].tile};

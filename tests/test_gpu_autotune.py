@@ -69,3 +69,11 @@ def test_a_tuned_forward_leaves_recompute_and_imaging_to_the_library(tmp_path):
             assert was["kind"] == "vector" and prop.launch(role) == was
         prop.set_tiling(8, 8)                                  # the caller's own choice holds for every role
         assert all(prop.launch(role)["kind"] == "block" for role in own)
+
+
+def test_a_tuned_2d_plan_keeps_several_steps_per_launch(tmp_path):
+    print("case: 2D autotune", flush=True)
+    prop = _prop((90, 120), 8)
+    own = prop.launch()
+    _tuned(prop, tmp_path / "c", zc=12)
+    assert own["kind"] == "steps" and prop.launch() == own and prop.tiling["zc"] == 12

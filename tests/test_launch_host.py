@@ -1,4 +1,6 @@
 """Which kernels a plan can be made to launch (no GPU)."""
+import ctypes
+
 import pytest
 
 from paper_2201_05278_amd import Propagator, SimwaveError
@@ -69,3 +71,19 @@ def test_steps_per_launch_in_2d():
     with pytest.raises(SimwaveError, match="no such tile"):
         _plan((60, 80), 8, "vd_staggered").set_launch(1, 3)
     assert _plan((60, 80), 8, "vd_staggered").launch()["kind"] == "block"
+
+
+def test_an_explicit_2d_tiling_runs_single_steps():
+    prop, n = _plan((60, 80), 8), ctypes.c_int64()
+
+    def scratch():
+        assert L.lib().sw_plan_scratch(prop._plan, ctypes.byref(n)) == 0
+        return n.value
+
+    assert prop.launch()["kind"] == "steps" and scratch() > 0
+    prop.set_tiling(zc=16)
+    assert (prop.launch()["kind"], prop.launch()["zc"], prop.launch()["steps"]) == ("block", 16, 1) and scratch() == 0
+    with pytest.raises(SimwaveError, match="tiling of its own"):
+        prop.set_launch(1, 3)
+    prop.set_tiling()
+    assert prop.launch()["kind"] == "steps" and scratch() > 0
