@@ -469,7 +469,8 @@ sw_status sw_batch_forward_static(sw_batch *batch, const sw_batch_io *io, void *
  * (may be NULL: no cache).  Candidates of a plan are timed as single forward steps:
  * its choice holds for those (also in the adjoint), while recompute and imaging
  * launches, and 2D launches of several steps, stay the library's.  The choice is kept in the plan / batch and
- * written back to the cache.  Synchronises `stream`. */
+ * written back to the cache; an entry written by a library with other kernels
+ * is tuned again.  Synchronises `stream`. */
 sw_status sw_plan_autotune(sw_plan *plan, const sw_fwd_io *io, const char *cache_path, void *stream);
 sw_status sw_batch_autotune(sw_batch *batch, const sw_batch_io *io, const char *cache_path,
                             void *stream);

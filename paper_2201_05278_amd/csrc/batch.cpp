@@ -153,7 +153,10 @@ sw_status enqueue_batch(sw_batch *b, const sw_batch_io *io, hipStream_t s)
     return SW_OK;
 }
 
-// ---- a small JSON cache: {"key": {"tx": 16, "nw": 4, "zc": 74, "nt": 1, "bpc": 4}, ...}
+// ---- a small JSON cache: {"key": {"tx": 16, "nw": 4, "zc": 74, "nt": 1, "bpc": 4, "kernels": 2}, ...}
+// "kernels" counts the sets of kernels that have been timed; an entry of an
+// older set, which did not time today's candidates, is tuned again.
+constexpr int kKernelSet = 2;
 std::map<std::string, std::map<std::string, int>> read_cache(const char *path)
 {
     std::map<std::string, std::map<std::string, int>> out;
@@ -417,7 +420,7 @@ sw_status sw_plan_autotune(sw_plan *p, const sw_fwd_io *io, const char *cache_pa
     const std::string key = plan_key(p, "plan");
     auto cache = read_cache(cache_path);
     auto it = cache.find(key);
-    if (it != cache.end()) {
+    if (it != cache.end() && it->second["kernels"] == kKernelSet) {
         auto &v = it->second;
         const sw_tiling t{v["tx"], v["nw"], v["zc"], v["nt"], v["pf"], v["wt"], v["ts"],
                           v.count("occ") ? v["occ"] : -1, v.count("order") ? v["order"] : 0};
@@ -501,7 +504,7 @@ sw_status sw_plan_autotune(sw_plan *p, const sw_fwd_io *io, const char *cache_pa
     p->tile_tuned = true;
     cache[key] = {{"tx", best_t.tx}, {"nw", best_t.nw}, {"zc", best_t.zc}, {"nt", best_t.nt},
                   {"pf", best_t.pf}, {"wt", best_t.wt}, {"ts", best_t.ts}, {"occ", best_t.occ},
-                  {"order", best_t.order}};
+                  {"order", best_t.order}, {"kernels", kKernelSet}};
     write_cache(cache_path, cache);
     return SW_OK;
 }
@@ -523,7 +526,7 @@ sw_status sw_batch_autotune(sw_batch *b, const sw_batch_io *io, const char *cach
     const std::string key = kb;
     auto cache = read_cache(cache_path);
     auto it = cache.find(key);
-    if (it != cache.end()) {
+    if (it != cache.end() && it->second["kernels"] == kKernelSet) {
         auto &v = it->second;
         if (b->ndim == 2 || const_shape_ok(v["tx"], v["nw"])) {
             b->tiling = Tiling{v["tx"], v["nw"], v["zc"], v["nt"], v["pf"] ? v["pf"] : 1, 0};
@@ -590,7 +593,7 @@ sw_status sw_batch_autotune(sw_batch *b, const sw_batch_io *io, const char *cach
     b->bpc = bbpc;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    cache[key] = {{"tx", bt.tx}, {"nw", bt.nw}, {"zc", bt.zc}, {"nt", bt.nt}, {"pf", bt.pf}, {"bpc", bbpc}};
+    cache[key] = {{"tx", bt.tx}, {"nw", bt.nw}, {"zc", bt.zc}, {"nt", bt.nt}, {"pf", bt.pf}, {"bpc", bbpc}, {"kernels", kKernelSet}};
     write_cache(cache_path, cache);
     return SW_OK;
 }

@@ -77,3 +77,10 @@ def test_a_tuned_2d_plan_keeps_several_steps_per_launch(tmp_path):
     own = prop.launch()
     _tuned(prop, tmp_path / "c", zc=12)
     assert own["kind"] == "steps" and prop.launch() == own and prop.tiling["zc"] == 12
+
+
+def test_cache_entries_of_older_kernels_are_tuned_again(tmp_path):
+    print("case: autotune cache of an older library", flush=True)
+    prop = _prop((40, 36, 48), 8)
+    known, after = _tuned(prop, tmp_path / "c", tx=16, nw=8, zc=5, kernels=None)
+    assert after["kernels"] == known["kernels"] and after["zc"] != 5 and prop.tiling["zc"] != 5
