@@ -128,29 +128,40 @@ namespace {
 // Mirror sides along x or y end that: the blocks at those sides make ghosts on
 // every plane and fall behind, so one round costs edge times its load (592^3
 // SO8, every side mirrored: one round 0.730 ms, 8 chunks of 74 planes 0.677),
-// and a tile that has the CU to itself waits at their second barrier with
-// nothing else to run.  So tiles are taken there of which two fit and whose
-// waves spread evenly over the SIMDs (207 x 801 x 801, SO8: 24 x 64 columns
-// 0.566 ms, 16 x 64 0.429; in doubles 24 x 64 0.957, 16 x 64 0.861).  Imaging
-// launches, with up to seven streams, want the even spread too.
+// and the other waves of a SIMD must fill the wait at their second barrier.  So
+// their own constants (fitted to 350 grids of 0.3 M .. 250 M nodes in single
+// precision up to SO18 and 66 in double at SO2 and SO4, every tile and 14 chunk
+// counts each) charge a plane by the waves it leaves per SIMD (qw), more where
+// those differ between SIMDs (uneven), and favour at equal waits a tile that has
+// the CU to itself (ql).  Choices ran 3.0% behind the sweep's best on average,
+// 17% at worst (with the constants above 17% and 130%).  Of 1300 other grids six
+// ran more than 1.5% behind the scalar tiles, 8% at worst (67 of 366 with the
+// constants above, 25%: 768 x 532 x 507 SO18, 1373 us against 1041, now 958).
+// In doubles from SO6 on the general constants hold, with tiles of which two
+// fit and whose waves spread evenly over the SIMDs (207 x 801 x 801 SO8: 24 x 64
+// 0.957 ms, 16 x 64 0.861).  Imaging launches, with up to seven streams, want the
+// even spread too.
 struct CostModel {
-    double k, k1, a, c, hx, hy, w, tail, pm, latency, idle, edge;
+    double k, k1, a, c, hx, hy, w, tail, pm, latency, lr, idle, edge, qw, uneven, ql;
 };
-constexpr CostModel kCost32{4.07e-4, 6.3e-7, 0.061, 1.3, 0.17, 0.25, 1.8, 0.075, 1.21, 1.35, 1.55, 1.5};
-constexpr CostModel kCost64{5.08e-4, 0.0, 0.084, 1.8, 0.24, 0.11, 1.0, 0.26, 1.03, 1.54, 0.21, 1.15};
+constexpr CostModel kCost32{4.07e-4, 6.3e-7, 0.061, 1.3, 0.17, 0.25, 1.8, 0.075, 1.21, 1.35, 0.02, 1.55, 1.5, 0.0, 1.0, 1.0};
+constexpr CostModel kCost64{5.08e-4, 0.0, 0.084, 1.8, 0.24, 0.11, 1.0, 0.26, 1.03, 1.54, 0.02, 0.21, 1.15, 0.0, 1.0, 1.0};
+constexpr CostModel kMirror32{4.07e-4, 3.1e-7, 0.0088, 1.19, 0.366, 0.128, 1.68, 0.145, 1.205, 2.06, 0.052, 0.656, 1.254, 0.163, 1.276, 0.978};
+constexpr CostModel kMirror64{2.82e-4, 0.0, 0.0334, 0.32, 0.239, 0.165, 1.04, 0.278, 1.09, 0.964, 0.0692, 0.706, 0.989, 1.18, 1.04, 0.98};
 
 template <typename T>
 VecChoice choose(const sw_plan *p, int mode)
 {
     constexpr int kCUs = 256;
     constexpr int kFourWaves = sizeof(T) == 4 ? 2 : 1;      // the tile of 4 waves, one per SIMD
-    constexpr CostModel m = sizeof(T) == 4 ? kCost32 : kCost64;
     VecChoice best;
     const int slots = resident<T>(p->r, kFourWaves, mode);  // waves per SIMD
     if (slots <= 0) return best;
     const int Z = p->dims[0], X = p->dims[1], Y = p->dims[2], R = p->r;
     const bool edges = p->prob.bc[1][0] || p->prob.bc[1][1] || p->prob.bc[2][0] || p->prob.bc[2][1];
     const bool image = mode == MODE_IMAGE || mode == MODE_IMAGE2;
+    const bool own = edges && (sizeof(T) == 4 || R <= 2);           // constants of mirrored sides
+    const CostModel m = sizeof(T) == 4 ? (own ? kMirror32 : kCost32) : own ? kMirror64 : kCost64;
     const int zmax = vec_zmax(p);
     double cost = 0.0;
     for (int i = 0; i < kVecTileCount; ++i) {
@@ -158,12 +169,17 @@ VecChoice choose(const sw_plan *p, int mode)
         const int cols = t.lpr * int(16 / sizeof(T)), waves = t.tx * t.lpr / 64;
         // resident blocks, with a block's waves spread over the four SIMDs (6
         // waves take two slots of each of two SIMDs)
-        const int res = std::min(resident<T>(R, i, mode), waves >= 4 ? slots / ((waves + 3) / 4) : slots * 4 / waves);
-        if (res <= 0 || (slots >= 4 && (edges || image) && waves > 2 && waves % 4) || (slots >= 4 && edges && res < 2)) continue;
+        // (a block of more waves than that is compiled for its own registers)
+        const int fit = resident<T>(R, i, mode);
+        if (fit <= 0 || (sizeof(T) == 4 && edges && R == 10 && i != kFourWaves)) continue;     // (the others spill)
+        const int res = std::max(1, std::min(fit, waves >= 4 ? slots / ((waves + 3) / 4) : slots * 4 / waves));
+        const bool uneven = waves > 2 && waves % 4;
+        if (!own && slots >= 4 && (((edges || image) && uneven) || (edges && res < 2))) continue;
         const double tiles = double((X + t.tx - 1) / t.tx) * ((Y + cols - 1) / cols);
         const double used = double(X) * Y / (tiles * t.tx * cols);
         const double nodes = t.tx * cols * (sizeof(T) / 4.0) * (used + (1.0 - used) * m.idle);
-        const double plane = nodes * (m.k + m.k1 * R * R) * (1.0 + m.hx * 2 * R / t.tx + m.hy * 64.0 / cols);
+        const double plane = nodes * (m.k + m.k1 * R * R) * (1.0 + m.hx * 2 * R / t.tx + m.hy * 64.0 / cols) *
+                             std::pow(4.0 / std::min(4.0, res * waves / 4.0), m.qw) * (uneven ? m.uneven : 1.0);
         for (int n = 1; n <= Z; ++n) {
             const int zc = (Z + n - 1) / n;
             if (zc > zmax) continue;
@@ -173,7 +189,8 @@ VecChoice choose(const sw_plan *p, int mode)
             const double load = once ? (m.w * std::ceil(per_cu) + (1.0 - m.w) * per_cu) * (edges ? m.edge : 1.0)
                                      : (per_cu + m.tail * res) * m.pm;
             const double planes = zc + m.a * 2 * R + m.c;
-            const double wait = m.latency * (1.0 + 0.02 * R) * planes * (once ? 1.0 : std::ceil(per_cu / res));
+            const double wait = m.latency * (1.0 + m.lr * R) * planes * (once ? 1.0 : std::ceil(per_cu / res)) *
+                                (res < 2 ? m.ql : 1.0);
             const double us = std::max(load * planes * plane, wait);
             if (best.tile < 0 || us < cost) {
                 cost = us;
@@ -255,6 +272,19 @@ bool vd_vectors(const sw_plan *p, int mode)
     return R >= 9 || nodes < (R <= 2 ? 40e6 : R <= 6 ? 1e18 : 30e6);
 }
 
+// Constant density: vector tiles, but where the scalar ones are as fast or
+// faster.  SO2 above 130 M nodes (nine grids: 0.95 .. 1.05 of the scalar tiles'
+// time); SO20 with sides mirrored along x or y above 10 M nodes, whose kernel has
+// registers for two waves per SIMD only (466 x 495 x 397: 557 us against 666 on vector tiles).
+bool const_vectors(const sw_plan *p, int mode)
+{
+    const double nodes = double(p->dims[0]) * p->dims[1] * p->dims[2];
+    const bool edges = p->prob.bc[1][0] || p->prob.bc[1][1] || p->prob.bc[2][0] || p->prob.bc[2][1];
+    if (p->prob.dtype == SW_F64) return true;
+    if (edges) return p->r < 10 || nodes < 10e6;
+    return p->r > 1 || p->mirror || mode != MODE_FWD || nodes < 130e6;
+}
+
 }  // namespace
 
 int vec_zmax(const sw_plan *p)
@@ -294,6 +324,7 @@ VecChoice choose_vec(const sw_plan *p, int mode)
     if (const sw_plan::Pin &pin = p->pin[mode]; pin.tile >= 0)
         return {pin.tile, std::min(pin.extent, p->dims[0]), p->prob.scheme == SW_CONST && p->mirror};
     if (p->prob.scheme != SW_CONST) return vd_vectors(p, mode) ? choose_vd(p) : VecChoice{};
+    if (!const_vectors(p, mode)) return {};
     if (p->mirror) mode = kVecMirror;
     VecChoice c = p->prob.dtype == SW_F64 ? choose<double>(p, mode) : choose<float>(p, mode);
     c.mirror = p->mirror;

@@ -156,3 +156,26 @@ def test_kernels_that_the_library_chooses(n, so, scheme, dtype, bc, kind):
     gradient = dtype == "float32" and bc is None and scheme != "vd_centred" and len(n) == 3
     for role in ("recompute", "image", "image_pair") if gradient else ():
         assert prop.launch(role)["kind"] == kind
+
+
+def _choice(n, so, scheme, dtype, bc, nbl=0):
+    h = (10.0,) * len(n)
+    launch = Propagator(n, h, so, 0.4 * critical_dt(h, so, 3000.0), 5, scheme=scheme, nbl=nbl, dtype=dtype, bc=bc).launch()
+    return (launch["kind"], launch["rows"], launch["cols"])
+
+
+ALL = (("neumann", "dirichlet"), ("dirichlet", "dirichlet"), ("dirichlet", "dirichlet"))
+
+
+@pytest.mark.parametrize("n,so,dtype,bc,want", [
+    # us per step of the choice, of another vector tile that a model without these sides or orders took, of the scalar tiles
+    ((768, 532, 507), 18, "float32", ALL, ("vector", 24, 128)),     # 958, 1373, 1041
+    ((438, 574, 369), 18, "float32", ALL, ("vector", 24, 128)),     # 437, 623, 511
+    ((466, 495, 397), 20, "float32", ALL, ("block", 8, 64)),        # 558, 671, 557
+    ((138, 179, 137), 20, "float32", ALL, ("vector", 16, 64)),      # 45, 54, 78
+    ((178, 325, 319), 2, "float64", ALL, ("vector", 8, 64)),        # 100, 131, 110
+    ((713, 601, 378), 2, "float32", None, ("block", 8, 64)),        # 499, 528, 492
+    ((592, 592, 592), 8, "float32", None, ("vector", 24, 128)),     # 618, -, 649
+])
+def test_constant_density_choices(n, so, dtype, bc, want):
+    assert _choice(n, so, "const", dtype, bc) == want
