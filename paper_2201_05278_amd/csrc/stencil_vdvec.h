@@ -654,6 +654,34 @@ hipError_t launch_vdvec_radius(int scheme, int tile, int mode, StencilParams &P,
     return hipErrorInvalidValue;
 }
 
-#define SW_VDVEC_RADIUS(R) template hipError_t launch_vdvec_radius<R>(int, int, int, StencilParams &, hipStream_t);
+template <int R, int I>
+int vdvec_resident_tile()
+{
+    constexpr VdTile t = kVdTiles[I];
+    constexpr int threads = t.tx * t.ty / vd_columns(2, R);
+    if constexpr (threads <= kVdThreads) {
+        int n = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_cent_vec<R, t.tx, t.ty>, threads, 0) == hipSuccess ? n : 0;
+    }
+    return 0;
+}
+
+template <int R>
+int vdvec_resident_radius(int scheme, int tile)
+{
+    if (scheme != 2) return 0;
+    switch (tile) {
+    case 0: return vdvec_resident_tile<R, 0>();
+    case 1: return vdvec_resident_tile<R, 1>();
+    case 2: return vdvec_resident_tile<R, 2>();
+    case 3: return vdvec_resident_tile<R, 3>();
+    case 4: return vdvec_resident_tile<R, 4>();
+    default: return 0;
+    }
+}
+
+#define SW_VDVEC_RADIUS(R)                                                                  \
+    template hipError_t launch_vdvec_radius<R>(int, int, int, StencilParams &, hipStream_t); \
+    template int vdvec_resident_radius<R>(int, int);
 
 }  // namespace sw

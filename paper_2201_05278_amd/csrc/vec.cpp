@@ -15,7 +15,8 @@ namespace sw {
 #define SW_XR(R)                     \
     SW_X(float, R) SW_X(double, R)   \
     extern template hipError_t launch_vec_batch_radius<R>(const StencilParams *, const int *, int, int, int, hipStream_t); \
-    extern template hipError_t launch_vdvec_radius<R>(int, int, int, StencilParams &, hipStream_t);
+    extern template hipError_t launch_vdvec_radius<R>(int, int, int, StencilParams &, hipStream_t); \
+    extern template int vdvec_resident_radius<R>(int, int);
 SW_XR(1) SW_XR(2) SW_XR(3) SW_XR(4) SW_XR(5) SW_XR(6) SW_XR(7) SW_XR(8) SW_XR(9) SW_XR(10)
 #undef SW_XR
 #undef SW_X
@@ -207,30 +208,53 @@ VecChoice choose(const sw_plan *p, int mode)
 // a last partial one a little less where its blocks have a SIMD to themselves
 // (fitted to sweeps on six grids of 2.7 M .. 207 M nodes at SO4, SO8 and SO16:
 // its choices ran within 1% of the sweep's best on average, staggered, and 3%,
-// centred).
+// centred).  Sweeps of 609 staggered and 795 centred grids of 0.5 M .. 250 M nodes
+// showed other orders to be further off (staggered SO16 9% on average, 64% at
+// worst; centred SO14 19%, 43%), so these have constants of their own: staggered
+// forward launches but SO8 (1% on average, 12% at worst), centred ones at SO2,
+// SO4, SO6 and SO14, whose kernels leave three waves per SIMD or four (waves: how
+// much a plane gains by them) and, but for SO2, want 8 x 64 columns (5%, 28%).
 struct VdCost {
-    double hx, hy, warm, plane, tail, alone, last;
+    double hx, hy, warm, plane, tail, alone, last, waves;
 };
-constexpr VdCost kStagCost{0.147, 1.2, 0.176, 1.78, 0.26, 1.0, 1.0};
-constexpr VdCost kCentCost{0.3, 1.235, 0.239, 0.0, 0.0, 0.25, 0.6};
+constexpr VdCost kStagCost{0.147, 1.2, 0.176, 1.78, 0.26, 1.0, 1.0, 0.0};
+constexpr VdCost kStagForward{0.142, 0.035, 0.32, 0.68, 0.146, 0.71, 0.54, 0.0};
+constexpr VdCost kCentCost{0.3, 1.235, 0.239, 0.0, 0.0, 0.25, 0.6, 0.0};
+constexpr VdCost kCentNarrow{0.0, 0.56, 0.0365, 0.05, 0.0, 0.25, 0.08, 0.27};
 
-VecChoice choose_vd(const sw_plan *p)
+int vd_resident(const sw_plan *p, int tile)
+{
+    switch (p->r) {
+    case 1: return vdvec_resident_radius<1>(p->prob.scheme, tile);
+    case 2: return vdvec_resident_radius<2>(p->prob.scheme, tile);
+    case 3: return vdvec_resident_radius<3>(p->prob.scheme, tile);
+    case 7: return vdvec_resident_radius<7>(p->prob.scheme, tile);
+    default: return 0;
+    }
+}
+
+// cost: that of the choice, for the comparison with the scalar tiles.
+VecChoice choose_vd(const sw_plan *p, int mode, double &cost)
 {
     constexpr int kCUs = 256;
     VecChoice best;
     const bool stag = p->prob.scheme == SW_VD_STAGGERED;
-    const VdCost m = stag ? kStagCost : kCentCost;
+    const bool narrow = !stag && (p->r <= 3 || p->r == 7);
+    const VdCost m = stag ? (mode == MODE_FWD && p->r != 4 ? kStagForward : kStagCost) : narrow ? kCentNarrow : kCentCost;
     const int Z = p->dims[0], X = p->dims[1], Y = p->dims[2], R = p->r;
     const int warm = stag ? 2 * R - 1 : 2 * R;
     const int zmax = vec_zmax(p);
-    double cost = 0.0;
+    cost = 0.0;
     for (int i = 0; i < kVdTileCount; ++i) {
         const VdTile t = kVdTiles[i];
         const int threads = t.tx * t.ty / vd_columns(p->prob.scheme, R);
-        if (threads > kVdThreads || (!stag && (t.tx > 16 ? R < 3 || t.ty > 32 : R < 3 && t.ty > 64))) continue;
-        const int res = 512 / threads;                     // two waves per SIMD
+        if (threads > kVdThreads || (narrow ? R > 1 && i > 0 : !stag && t.tx > 16 && t.ty > 32)) continue;
+        const int res = narrow ? vd_resident(p, i) : 512 / threads;     // two waves per SIMD
+        if (res <= 0) continue;
+        const double waves = res * threads / 256.0;
         const double tiles = double((X + t.tx - 1) / t.tx) * ((Y + t.ty - 1) / t.ty);
-        const double plane = t.tx * t.ty * (1.0 + m.hx * 2 * R / t.tx + m.hy * 2 * R / t.ty);
+        const double plane = t.tx * t.ty * (1.0 + m.hx * 2 * R / t.tx + m.hy * 2 * R / t.ty) *
+                             (1.0 + m.waves * (waves - 2.0)) * 2.0 / waves;
         for (int n = 1; n <= Z; ++n) {
             const int zc = (Z + n - 1) / n;
             if (zc > zmax) continue;
@@ -251,25 +275,49 @@ VecChoice choose_vd(const sw_plan *p)
     return best;
 }
 
-// Where the variable-density vector tiles are the faster ones (scalar against
-// vector tiles, us per forward step):
-//   staggered, R 2 .. 8: 240^3 SO8 122 against 104, SO16 228 against 213; but on
-//   larger grids the scalar tiles' four waves per SIMD stream better (360 x 360 x
-//   380 SO4 250 against 268, SO12 550 against 591), SO8 apart (592^3 1360 against
-//   1312).  Recording and imaging launches gain at every size (a gradient step at
-//   400^3 SO4 1503 against 1418, SO16 3659 against 3577).  R = 1 has little to
-//   share between neighbours (280^3 97 against 120), and from R = 9 on three
-//   queues leave no registers (280^3 SO20 561 against 1182).
-//   centred: 280^3 SO8 154 against 132, SO20 387 against 251; but large grids at
-//   SO2 and SO4 are the scalar tiles' (360 x 360 x 380 SO4 230 against 233) and
-//   at SO14 and SO16, where a thread has two columns (450 against 489).
-bool vd_vectors(const sw_plan *p, int mode)
+// Cost of a scalar variable-density launch in the units of choose_vd: whole
+// rounds of resident blocks, a last one half by its share (less than one round:
+// as the root of its share, since a lone block has more of the machine).
+double vd_scalar_cost(const sw_plan *p)
 {
-    const int R = p->r;
-    const double nodes = double(p->dims[0]) * p->dims[1] * p->dims[2];
-    if (p->prob.scheme == SW_VD_STAGGERED)
-        return R >= kStagRadii[0] && R <= kStagRadii[1] && (R == 4 || mode != MODE_FWD || nodes < (R == 2 ? 30e6 : 40e6));
-    return R >= 9 || nodes < (R <= 2 ? 40e6 : R <= 6 ? 1e18 : 30e6);
+    constexpr int kCUs = 256;
+    const Tiling t = choose_tiling(p);
+    const int res = resident_blocks(p, t);
+    if (res <= 0) return 0.0;
+    const double tiles = double((p->dims[1] + t.tx - 1) / t.tx) * ((p->dims[2] + 63) / 64);
+    const double per = tiles * ((p->dims[0] + t.zc - 1) / t.zc) / (double(kCUs) * res);
+    const double rest = per - std::floor(per);
+    const double rounds = per <= 1.0 ? std::max(std::sqrt(per), 0.3) : std::floor(per) + (rest < 1e-9 ? 0.0 : 0.5 + 0.5 * rest);
+    return rounds * res * t.zc * t.tx * 64.0;
+}
+
+// Where the variable-density vector tiles are the faster ones.  Recording and
+// imaging launches gain at every size (staggered gradients of 160^3 .. 400^3, SO4
+// .. SO16: 2% .. 56%).  Staggered R = 1 has little to share between neighbours
+// (280^3 97 against 120 us), and from R = 9 on three queues leave no registers
+// (280^3 SO20 561 against 1182 us).
+// Forward launches of both kinds gain or lose with how their blocks fill the
+// last round, by more than the kernels differ at some orders (staggered SO12,
+// 340^3 503 against 425 us but 440^3 887 against 957).  So the two costs decide:
+// vector tiles run where the scalar cost is above the mean (geometric) of the
+// vector cost and the ideal by the order's factor.  Of 276 other grids this left
+// 3 more than 1.5% slower than the scalar tiles, 5% at worst (a rule by size alone
+// 59 of 1229, 9%).  At the other orders vector tiles run throughout: staggered SO8
+// (6 of 113 slower, 7% at worst; 592^3 1287 against 1349 us) and SO16 (none of 31,
+// 1.52 times as fast on average), centred SO6 .. SO14, SO18 and SO20 (1 of 242, 4%;
+// 1.2 times as fast and more on average).
+bool vd_vectors(const sw_plan *p, int mode, double cost)
+{
+    const bool stag = p->prob.scheme == SW_VD_STAGGERED;
+    if (stag && (p->r < kStagRadii[0] || p->r > kStagRadii[1])) return false;
+    if (mode != MODE_FWD) return true;
+    constexpr double kStag[9] = {0, 0, 1.07, 0.99, 0, 1.02, 1.0, 0.967, 0};
+    constexpr double kCent[11] = {0, 1.21, 1.12, 0, 0, 0, 0, 0, 0.896, 0, 0};
+    const double factor = stag ? kStag[p->r] : kCent[p->r];
+    const double scalar = factor > 0.0 ? vd_scalar_cost(p) : 0.0;
+    if (scalar <= 0.0) return true;
+    const double ideal = double(p->dims[0]) * p->dims[1] * p->dims[2] / 256.0;
+    return scalar > factor * std::sqrt(cost * ideal);
 }
 
 // Constant density: vector tiles, but where the scalar ones are as fast or
@@ -323,7 +371,11 @@ VecChoice choose_vec(const sw_plan *p, int mode)
     if (p->ndim != 3 || !library_picks(p, mode) || (p->mirror && mode != MODE_FWD)) return {};
     if (const sw_plan::Pin &pin = p->pin[mode]; pin.tile >= 0)
         return {pin.tile, std::min(pin.extent, p->dims[0]), p->prob.scheme == SW_CONST && p->mirror};
-    if (p->prob.scheme != SW_CONST) return vd_vectors(p, mode) ? choose_vd(p) : VecChoice{};
+    if (p->prob.scheme != SW_CONST) {
+        double cost;
+        const VecChoice c = choose_vd(p, mode, cost);
+        return vd_vectors(p, mode, cost) ? c : VecChoice{};
+    }
     if (!const_vectors(p, mode)) return {};
     if (p->mirror) mode = kVecMirror;
     VecChoice c = p->prob.dtype == SW_F64 ? choose<double>(p, mode) : choose<float>(p, mode);

@@ -77,5 +77,8 @@ constexpr int vd_columns(int scheme, int r)
 hipError_t launch_vdvec(int scheme, int r, const VecChoice &c, int mode, StencilParams &P, hipStream_t s);
 template <int R>
 hipError_t launch_vdvec_radius(int scheme, int tile, int mode, StencilParams &P, hipStream_t s);
+// Resident blocks per CU of the centred kernel (scheme 2).
+template <int R>
+int vdvec_resident_radius(int scheme, int tile);
 
 }  // namespace sw

@@ -179,3 +179,16 @@ ALL = (("neumann", "dirichlet"), ("dirichlet", "dirichlet"), ("dirichlet", "diri
 ])
 def test_constant_density_choices(n, so, dtype, bc, want):
     assert _choice(n, so, "const", dtype, bc) == want
+
+
+@pytest.mark.parametrize("n,so,scheme,want", [
+    # us per step of the choice, of the vector tile that a rule by size took, of the scalar tiles
+    ((287, 272, 476), 12, "vd_staggered", ("block", 8, 64)),        # 437, 466, 436
+    ((340, 340, 340), 12, "vd_staggered", ("vector", 32, 32)),      # 426, -, 502
+    ((592, 592, 592), 8, "vd_staggered", ("vector", 16, 128)),      # 1287, -, 1349
+    ((359, 324, 256), 14, "vd_centred", ("vector", 8, 64)),         # 214, 274, 253
+    ((328, 433, 436), 6, "vd_centred", ("vector", 8, 64)),          # 287, 334, 315
+    ((280, 280, 280), 8, "vd_centred", ("vector", 32, 32)),         # 122, -, 148
+])
+def test_variable_density_choices(n, so, scheme, want):
+    assert _choice(n, so, scheme, "float32", None) == want
