@@ -111,6 +111,17 @@ int default_zc(const sw_plan *p, int tx, int64_t want, int ts)
     return std::max(zc, std::min(p->dims[0], 4 * p->r));
 }
 
+int compute_units(const sw_plan *p)
+{
+    int dev = 0, n = 0;
+    if (!p->ncu)
+        p->ncu = (hipGetDevice(&dev) == hipSuccess &&
+                  hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+                     ? n
+                     : -1;
+    return p->ncu > 0 ? p->ncu : 256;
+}
+
 // Resident blocks per CU of the plan's 3D forward kernel for tiling t
 // (queried once per plan and tiling; 0 without a device).
 int resident_blocks(const sw_plan *p, const Tiling &t)
@@ -120,12 +131,7 @@ int resident_blocks(const sw_plan *p, const Tiling &t)
                          uint64_t(t.occ & 0xff);
     for (const auto &e : p->resident_cache)
         if (e.first == key) return e.second;
-    int dev = 0, n = 0;
-    if (!p->ncu)
-        p->ncu = (hipGetDevice(&dev) == hipSuccess &&
-                  hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-                     ? n
-                     : -1;
+    (void)compute_units(p);
     const int r = p->ncu <= 0                    ? 0
                   : p->prob.dtype == SW_F64    ? f64_resident_blocks(p->r, t.tx, t.nw)
                   : p->prob.scheme == SW_CONST ? const_resident_blocks(p->r, t)

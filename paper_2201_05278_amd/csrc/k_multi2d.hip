@@ -324,7 +324,7 @@ hipError_t launch_tile(Multi2DParams<T> &P, hipStream_t s)
     return hipGetLastError();
 }
 
-constexpr Multi2DTile kTiles[] = {{64, 32, 1024}, {32, 32, 512}, {64, 16, 512}, {48, 16, 384}, {32, 16, 256}};    // ey: vectors
+constexpr Multi2DTile kTiles[] = {{64, 32}, {32, 32}, {64, 16}, {48, 16}, {32, 16}};    // ey: vectors
 
 // Radii whose neighbour vectors fit the 128 registers of a 1024-thread block.
 template <typename T>
@@ -359,9 +359,8 @@ hipError_t launch_radius(int tile, Multi2DParams<T> &P, hipStream_t s)
 // measured 8.5 us + 1.75 us R, plus about 4e-6 us per node and 4 bytes; where
 // the model with a quarter on top is not below that, the plan keeps it (SO20
 // at 1180 x 1980: 41 against 32 us per step).
-Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y)
+Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y, int cus)
 {
-    constexpr int kCUs = 256;
     Multi2DChoice best{};
     double cost = (8.5 + 1.75 * r + 1e-6 * value_bytes * double(Z) * Y) / 1.25;
     for (int tile = 0; tile < int(sizeof(kTiles) / sizeof(kTiles[0])); ++tile) {
@@ -370,7 +369,7 @@ Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y)
             const int tz = t.ez - 2 * r * nt, ty = t.ey - 2 * multi2d_pad_y(r * nt, value_bytes);
             if (!multi2d_tile_ok(r, value_bytes, tile, nt)) break;
             const double tiles = double((Z + tz - 1) / tz) * ((Y + ty - 1) / ty);
-            const double per_cu = std::ceil(tiles / kCUs);
+            const double per_cu = std::ceil(tiles / cus);
             int rows = 0;
             for (int s = 0; s < nt; ++s) rows += std::min(t.ez, tz + 2 * r * s);
             const double busy = per_cu * rows * t.ey * (1.26e-4 + 2.6e-5 * r);

@@ -39,9 +39,9 @@ struct Multi2DParams {
 };
 
 // Tile of a launch: rows and columns held on chip (the outputs plus nt R nodes
-// around them) and the threads that hold them.
+// around them).
 struct Multi2DTile {
-    int ez, ey, threads;
+    int ez, ey;
 };
 
 // Steps per launch and tile for a grid of Z x Y nodes; steps 0: the radius or
@@ -49,7 +49,7 @@ struct Multi2DTile {
 struct Multi2DChoice {
     int steps, tile;        // tile: index of the instantiated tiles
 };
-Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y);
+Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y, int cus);
 Multi2DTile multi2d_tile(int tile, int value_bytes);
 // Whether a tile is instantiated at a radius and holds any output after `steps` steps.
 bool multi2d_tile_ok(int r, int value_bytes, int tile, int steps);

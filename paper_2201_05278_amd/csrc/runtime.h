@@ -32,6 +32,8 @@ bool wave_shape_ok(int tx, int nw);
 int default_zc(const sw_plan *p, int tx, int64_t want, int ts = 1);
 Tiling choose_tiling(const sw_plan *p);
 int resident_blocks(const sw_plan *p, const Tiling &t);
+// Compute units of the device (256 without one).
+int compute_units(const sw_plan *p);
 bool library_picks(const sw_plan *p, int mode);
 void fill_params(const sw_plan *p, void *ws, StencilParams &P);
 void set_tiles(const sw_plan *p, const Tiling &t, StencilParams &P);

@@ -153,7 +153,7 @@ constexpr CostModel kMirror64{2.82e-4, 0.0, 0.0334, 0.32, 0.239, 0.165, 1.04, 0.
 template <typename T>
 VecChoice choose(const sw_plan *p, int mode)
 {
-    constexpr int kCUs = 256;
+    const int cus = compute_units(p);
     constexpr int kFourWaves = sizeof(T) == 4 ? 2 : 1;      // the tile of 4 waves, one per SIMD
     VecChoice best;
     const int slots = resident<T>(p->r, kFourWaves, mode);  // waves per SIMD
@@ -185,7 +185,7 @@ VecChoice choose(const sw_plan *p, int mode)
             const int zc = (Z + n - 1) / n;
             if (zc > zmax) continue;
             if (zc < 4 && n > 1) break;
-            const double per_cu = tiles * ((Z + zc - 1) / zc) / kCUs;
+            const double per_cu = tiles * ((Z + zc - 1) / zc) / cus;
             const bool once = per_cu <= res;
             const double load = once ? (m.w * std::ceil(per_cu) + (1.0 - m.w) * per_cu) * (edges ? m.edge : 1.0)
                                      : (per_cu + m.tail * res) * m.pm;
@@ -236,7 +236,7 @@ int vd_resident(const sw_plan *p, int tile)
 // cost: that of the choice, for the comparison with the scalar tiles.
 VecChoice choose_vd(const sw_plan *p, int mode, double &cost)
 {
-    constexpr int kCUs = 256;
+    const int cus = compute_units(p);
     VecChoice best;
     const bool stag = p->prob.scheme == SW_VD_STAGGERED;
     const bool narrow = !stag && (p->r <= 3 || p->r == 7);
@@ -259,7 +259,7 @@ VecChoice choose_vd(const sw_plan *p, int mode, double &cost)
             const int zc = (Z + n - 1) / n;
             if (zc > zmax) continue;
             if (zc < 4 && n > 1) break;
-            const double per_cu = tiles * ((Z + zc - 1) / zc) / kCUs;
+            const double per_cu = tiles * ((Z + zc - 1) / zc) / cus;
             const double full = std::floor(per_cu / res), rest = per_cu - full * res;
             const double half = full > 0.0 ? m.last : m.alone;      // of a round with every other slot empty
             const double part = rest > 1e-9 ? std::min(1.0, half + (1.0 - half) * std::ceil(rest) / res) : 0.0;
@@ -280,12 +280,12 @@ VecChoice choose_vd(const sw_plan *p, int mode, double &cost)
 // as the root of its share, since a lone block has more of the machine).
 double vd_scalar_cost(const sw_plan *p)
 {
-    constexpr int kCUs = 256;
+    const int cus = compute_units(p);
     const Tiling t = choose_tiling(p);
     const int res = resident_blocks(p, t);
     if (res <= 0) return 0.0;
     const double tiles = double((p->dims[1] + t.tx - 1) / t.tx) * ((p->dims[2] + 63) / 64);
-    const double per = tiles * ((p->dims[0] + t.zc - 1) / t.zc) / (double(kCUs) * res);
+    const double per = tiles * ((p->dims[0] + t.zc - 1) / t.zc) / (double(cus) * res);
     const double rest = per - std::floor(per);
     const double rounds = per <= 1.0 ? std::max(std::sqrt(per), 0.3) : std::floor(per) + (rest < 1e-9 ? 0.0 : 0.5 + 0.5 * rest);
     return rounds * res * t.zc * t.tx * 64.0;
@@ -316,7 +316,7 @@ bool vd_vectors(const sw_plan *p, int mode, double cost)
     const double factor = stag ? kStag[p->r] : kCent[p->r];
     const double scalar = factor > 0.0 ? vd_scalar_cost(p) : 0.0;
     if (scalar <= 0.0) return true;
-    const double ideal = double(p->dims[0]) * p->dims[1] * p->dims[2] / 256.0;
+    const double ideal = double(p->dims[0]) * p->dims[1] * p->dims[2] / compute_units(p);
     return scalar > factor * std::sqrt(cost * ideal);
 }
 

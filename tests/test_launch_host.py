@@ -87,3 +87,12 @@ def test_an_explicit_2d_tiling_runs_single_steps():
         prop.set_launch(1, 3)
     prop.set_tiling()
     assert prop.launch()["kind"] == "steps" and scratch() > 0
+
+
+def test_2d_tiles_follow_the_compute_units():
+    class Choice(ctypes.Structure):
+        _fields_ = [("steps", ctypes.c_int), ("tile", ctypes.c_int)]
+
+    search = getattr(L.lib(), "_ZN2sw14choose_multi2dEiiiii")          # radius, bytes per value, extents, compute units
+    search.restype, search.argtypes = Choice, [ctypes.c_int] * 5
+    assert search(4, 4, 281, 281, 64).steps < search(4, 4, 281, 281, 256).steps      # tiles queue: less halo per launch
