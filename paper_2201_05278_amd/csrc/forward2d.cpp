@@ -76,7 +76,13 @@ Multi2DChoice multi2d_choice(const sw_plan *p)
         p->field_elems > std::numeric_limits<int32_t>::max())   // 32-bit element offsets
         return {};
     if (p->pin[0].tile >= 0) return {p->pin[0].extent, p->pin[0].tile};
-    return choose_multi2d(p->r, value_bytes(p), p->dims[0], p->dims[2], compute_units(p));
+    uint64_t v = p->choice[0].load(std::memory_order_relaxed);
+    if (!v) {
+        const Multi2DChoice c = choose_multi2d(p->r, value_bytes(p), p->dims[0], p->dims[2], compute_units(p));
+        v = Choice::pack(c.steps, c.tile);
+        p->choice[0].store(v, std::memory_order_relaxed);
+    }
+    return {Choice::first(v), Choice::second(v)};
 }
 
 int64_t multi2d_scratch_bytes(const sw_plan *p)

@@ -2,6 +2,7 @@
 // table and point (source/receiver) tables.  Not part of the C ABI.
 #pragma once
 
+#include <atomic>
 #include <cstdint>
 #include <string>
 #include <utility>
@@ -109,6 +110,9 @@ struct sw_plan {
     // tiling key (queried once per kernel), and the device's CU count
     mutable std::vector<std::pair<uint64_t, int>> resident_cache;
     mutable int ncu = 0;
+    // the library's vector tile and chunk per mode, or 2D tile and step count
+    // (packed by Choice; 0: not searched for yet), which the plan's problem fixes
+    mutable std::atomic<uint64_t> choice[4] = {};
     // cached HIP graph of a forward run, captured on a private stream
     void *graph_exec = nullptr;
     void *capture_stream = nullptr;
@@ -116,6 +120,13 @@ struct sw_plan {
 };
 
 namespace sw {
+// A pair of small numbers (the first from -1) as one word other than 0, so that
+// threads may store and load a choice without a lock.
+struct Choice {
+    static uint64_t pack(int a, int b) { return (uint64_t(1) << 63) | uint64_t(a + 1) << 32 | uint32_t(b); }
+    static int first(uint64_t v) { return int(v >> 32 & 0x7fffffff) - 1; }
+    static int second(uint64_t v) { return int(uint32_t(v)); }
+};
 sw_status build_layout(sw_plan *p);
 void build_workspace_map(sw_plan *p);
 // source: true for the source table (images across mirrored sides), false

@@ -659,10 +659,7 @@ int vdvec_resident_tile()
 {
     constexpr VdTile t = kVdTiles[I];
     constexpr int threads = t.tx * t.ty / vd_columns(2, R);
-    if constexpr (threads <= kVdThreads) {
-        int n = 0;
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_cent_vec<R, t.tx, t.ty>, threads, 0) == hipSuccess ? n : 0;
-    }
+    if constexpr (threads <= kVdThreads) return blocks_per_cu<k_cent_vec<R, t.tx, t.ty>>(threads);
     return 0;
 }
 

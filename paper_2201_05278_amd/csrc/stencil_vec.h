@@ -22,6 +22,8 @@
 // the physical box changes.
 #pragma once
 
+#include <atomic>
+
 #include "stencil_const.h"
 #include "vec.h"
 
@@ -382,6 +384,19 @@ hipError_t launch_vec_batch_radius(const StencilParams *shots, const int *tile_s
     return hipGetLastError();
 }
 
+// Resident blocks per CU of a kernel, asked once per kernel (0, and asked again,
+// where the query fails).
+template <auto KERN>
+int blocks_per_cu(int threads)
+{
+    static std::atomic<int> known{0};
+    int n = known.load(std::memory_order_relaxed);
+    if (n > 0) return n;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, KERN, threads, 0) != hipSuccess) return 0;
+    known.store(n, std::memory_order_relaxed);
+    return n;
+}
+
 template <typename T, int R, int TX, int LPR, int MODE>
 constexpr auto vec_kernel()
 {
@@ -412,12 +427,7 @@ int vec_resident_tile()
 {
     if constexpr (vec_has<T, R, MODE, I>()) {
         constexpr VecTile t = kVecTiles<T>[I];
-        static const int blocks = [] {           // once per kernel
-            int n = 0;
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, vec_kernel<T, R, t.tx, t.lpr, MODE>(), t.tx * t.lpr, 0) ==
-                           hipSuccess ? n : 0;
-        }();
-        return blocks;
+        return blocks_per_cu<vec_kernel<T, R, t.tx, t.lpr, MODE>()>(t.tx * t.lpr);
     }
     return 0;
 }

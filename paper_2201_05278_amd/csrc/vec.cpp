@@ -181,10 +181,11 @@ VecChoice choose(const sw_plan *p, int mode)
         const double nodes = t.tx * cols * (sizeof(T) / 4.0) * (used + (1.0 - used) * m.idle);
         const double plane = nodes * (m.k + m.k1 * R * R) * (1.0 + m.hx * 2 * R / t.tx + m.hy * 64.0 / cols) *
                              std::pow(4.0 / std::min(4.0, res * waves / 4.0), m.qw) * (uneven ? m.uneven : 1.0);
-        for (int n = 1; n <= Z; ++n) {
+        for (int n = 1, last = 0; n <= Z; ++n) {
             const int zc = (Z + n - 1) / n;
-            if (zc > zmax) continue;
+            if (zc > zmax || zc == last) continue;
             if (zc < 4 && n > 1) break;
+            last = zc;
             const double per_cu = tiles * ((Z + zc - 1) / zc) / cus;
             const bool once = per_cu <= res;
             const double load = once ? (m.w * std::ceil(per_cu) + (1.0 - m.w) * per_cu) * (edges ? m.edge : 1.0)
@@ -255,10 +256,11 @@ VecChoice choose_vd(const sw_plan *p, int mode, double &cost)
         const double tiles = double((X + t.tx - 1) / t.tx) * ((Y + t.ty - 1) / t.ty);
         const double plane = t.tx * t.ty * (1.0 + m.hx * 2 * R / t.tx + m.hy * 2 * R / t.ty) *
                              (1.0 + m.waves * (waves - 2.0)) * 2.0 / waves;
-        for (int n = 1; n <= Z; ++n) {
+        for (int n = 1, last = 0; n <= Z; ++n) {
             const int zc = (Z + n - 1) / n;
-            if (zc > zmax) continue;
+            if (zc > zmax || zc == last) continue;
             if (zc < 4 && n > 1) break;
+            last = zc;
             const double per_cu = tiles * ((Z + zc - 1) / zc) / cus;
             const double full = std::floor(per_cu / res), rest = per_cu - full * res;
             const double half = full > 0.0 ? m.last : m.alone;      // of a round with every other slot empty
@@ -366,21 +368,37 @@ void vec_extents(const sw_plan *p, int tile, int &rows, int &cols)
     }
 }
 
-VecChoice choose_vec(const sw_plan *p, int mode)
+// The library's choice in a mode; searched: whether the search had what it needs
+// (a device that reports its occupancy).
+static VecChoice search_vec(const sw_plan *p, int mode, bool &searched)
 {
-    if (p->ndim != 3 || !library_picks(p, mode) || (p->mirror && mode != MODE_FWD)) return {};
-    if (const sw_plan::Pin &pin = p->pin[mode]; pin.tile >= 0)
-        return {pin.tile, std::min(pin.extent, p->dims[0]), p->prob.scheme == SW_CONST && p->mirror};
+    searched = true;
     if (p->prob.scheme != SW_CONST) {
         double cost;
         const VecChoice c = choose_vd(p, mode, cost);
+        searched = c.tile >= 0 && p->ncu > 0;
         return vd_vectors(p, mode, cost) ? c : VecChoice{};
     }
     if (!const_vectors(p, mode)) return {};
     if (p->mirror) mode = kVecMirror;
-    VecChoice c = p->prob.dtype == SW_F64 ? choose<double>(p, mode) : choose<float>(p, mode);
-    c.mirror = p->mirror;
+    const VecChoice c = p->prob.dtype == SW_F64 ? choose<double>(p, mode) : choose<float>(p, mode);
+    searched = c.tile >= 0;
     return c;
+}
+
+VecChoice choose_vec(const sw_plan *p, int mode)
+{
+    if (p->ndim != 3 || !library_picks(p, mode) || (p->mirror && mode != MODE_FWD)) return {};
+    const bool mirror = p->prob.scheme == SW_CONST && p->mirror;
+    if (const sw_plan::Pin &pin = p->pin[mode]; pin.tile >= 0) return {pin.tile, std::min(pin.extent, p->dims[0]), mirror};
+    uint64_t v = p->choice[mode].load(std::memory_order_relaxed);
+    if (!v) {
+        bool searched = false;
+        const VecChoice c = search_vec(p, mode, searched);
+        v = Choice::pack(c.tile, c.zc);
+        if (searched) p->choice[mode].store(v, std::memory_order_relaxed);
+    }
+    return {Choice::first(v), Choice::second(v), mirror};
 }
 
 }  // namespace sw

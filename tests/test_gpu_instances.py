@@ -1,5 +1,7 @@
 """Every vector and multi-step tile, chosen by hand on small ragged grids, bitwise against the scalar single-step kernels
 (which the oracle tests pin); and the kernels that the library chooses by itself."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -192,3 +194,15 @@ def test_constant_density_choices(n, so, dtype, bc, want):
 ])
 def test_variable_density_choices(n, so, scheme, want):
     assert _choice(n, so, scheme, "float32", None) == want
+
+
+def test_the_search_for_a_launch_runs_once_per_plan():
+    # 66000 chunk counts for each tile: several ms a search
+    prop = Propagator((200000, 30, 30), H, 8, 1e-4, 5, nbl=0)
+    first = prop.launch()
+    times = []
+    for _ in range(5):
+        t = time.perf_counter()
+        assert prop.launch() == first
+        times.append(time.perf_counter() - t)
+    assert first["kind"] == "vector" and min(times) < 1e-3
