@@ -242,10 +242,15 @@ sw_status sw_forward(sw_plan *plan, const sw_fwd_io *io, void *stream);
  * faster than sw_forward / sw_forward_f64 (0: the plan has no use for any).
  * Depends on the grid, the step count, the sources and the tiling. */
 sw_status sw_plan_scratch(const sw_plan *plan, int64_t *bytes);
+/* The bytes that one run of nsteps_run steps has a use for, at most those of
+ * sw_plan_scratch: without receivers, and with levels 0 (no snapshots or
+ * checkpoints), two wavefields in place of up to 14; 0 for a run too short to
+ * take several steps per launch. */
+sw_status sw_run_scratch(const sw_plan *plan, int32_t nsteps_run, int32_t levels, int64_t *bytes);
 
 /* sw_forward with `scratch_bytes` bytes of caller-owned device memory at
  * `scratch`, which the call's launches write and read (two calls that may
- * overlap need two).  With sw_plan_scratch's bytes, a 2D constant-density grid
+ * overlap need two).  With sw_run_scratch's or sw_plan_scratch's bytes, a 2D constant-density grid
  * advances several steps per launch; results are bitwise those of sw_forward.
  * With less, with NULL, with buffers not aligned to 16 bytes, with stencil_ms
  * or for other plans the call is sw_forward. */

@@ -108,6 +108,7 @@ SIGNATURES = {
     "sw_model_prepare": (c_int32, [c_void_p, c_void_p, c_void_p, c_double, c_void_p, c_void_p]),
     "sw_forward": (c_int32, [c_void_p, ctypes.POINTER(FwdIO), c_void_p]),
     "sw_plan_scratch": (c_int32, [c_void_p, ctypes.POINTER(c_int64)]),
+    "sw_run_scratch": (c_int32, [c_void_p, c_int32, c_int32, ctypes.POINTER(c_int64)]),
     "sw_forward_scratch": (c_int32, [c_void_p, ctypes.POINTER(FwdIO), c_void_p, c_int64, c_void_p]),
     "sw_model_prepare_f64": (c_int32, [c_void_p, c_void_p, c_double, c_void_p, c_void_p]),
     "sw_forward_f64": (c_int32, [c_void_p, ctypes.POINTER(Fwd64IO), c_void_p]),

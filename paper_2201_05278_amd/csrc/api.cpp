@@ -1005,7 +1005,15 @@ sw_status sw_plan_scratch(const sw_plan *p, int64_t *bytes)
 {
     set_error("");
     if (!p || !bytes) return fail(SW_ERR_ARG, "NULL argument");
-    *bytes = multi2d_scratch_bytes(p);
+    *bytes = multi2d_scratch_bytes(p, p->prob.nsteps, true);
+    return SW_OK;
+}
+
+sw_status sw_run_scratch(const sw_plan *p, int32_t nsteps_run, int32_t levels, int64_t *bytes)
+{
+    set_error("");
+    if (!p || !bytes) return fail(SW_ERR_ARG, "NULL argument");
+    *bytes = multi2d_divides(p, nsteps_run) ? multi2d_scratch_bytes(p, nsteps_run, levels != 0) : 0;
     return SW_OK;
 }
 

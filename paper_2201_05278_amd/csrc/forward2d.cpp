@@ -28,16 +28,24 @@ int64_t align_up(int64_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 int value_bytes(const sw_plan *p) { return p->prob.dtype == SW_F64 ? 8 : 4; }
 
 // Byte offsets in the scratch: buffer k (0, 1: the second pair; from 2 on the
-// levels between, T - 2 of them per set), then the injected values.
+// levels between, `between` of them per set), then the injected values.
 struct ScratchMap {
+    int between;
     int64_t field, inj, total;
-    explicit ScratchMap(const sw_plan *p, int steps)
+    ScratchMap(const sw_plan *p, int steps, int nsteps, bool levels)
     {
+        between = levels || p->rec.count ? std::max(0, steps - 2) : 0;
         field = align_up(p->field_elems * value_bytes(p));
-        inj = field * (2 + 2 * std::max(0, steps - 2));
-        total = inj + align_up(int64_t(p->prob.nsteps) * int64_t(p->src.unode.size()) * value_bytes(p));
+        inj = field * (2 + 2 * between);
+        total = inj + align_up(int64_t(nsteps) * int64_t(p->src.unode.size()) * value_bytes(p));
     }
 };
+
+template <typename T>
+bool wants_levels(const Run2D<T> &io)
+{
+    return (io.snaps && io.saving_stride > 0) || io.ckpt;
+}
 
 // Launches for n steps of at most T each, an even number of launches of two
 // steps at least; 0 where there is none.
@@ -85,26 +93,38 @@ Multi2DChoice multi2d_choice(const sw_plan *p)
     return {Choice::first(v), Choice::second(v)};
 }
 
-int64_t multi2d_scratch_bytes(const sw_plan *p)
+int64_t multi2d_scratch_bytes(const sw_plan *p, int nsteps, bool levels)
 {
     const Multi2DChoice c = multi2d_choice(p);
-    return c.steps ? ScratchMap(p, c.steps).total : 0;
+    return c.steps ? ScratchMap(p, c.steps, nsteps, levels).total : 0;
+}
+
+// Steps that run singly before the others divide into launches (-1: none do).
+static int singles_of(int nsteps, int steps)
+{
+    for (int r = 0; r <= 3; ++r)
+        if (launches_for(nsteps - r, steps)) return r;
+    return -1;
+}
+
+bool multi2d_divides(const sw_plan *p, int nsteps)
+{
+    const Multi2DChoice c = multi2d_choice(p);
+    return c.steps && singles_of(nsteps, c.steps) >= 0;
 }
 
 template <typename T>
 int multi2d_singles(const sw_plan *p, const Run2D<T> &io, const void *scratch, int64_t bytes)
 {
     const Multi2DChoice c = multi2d_choice(p);
-    if (!c.steps || !scratch || bytes < ScratchMap(p, c.steps).total) return -1;
+    if (!c.steps || !scratch || bytes < ScratchMap(p, c.steps, io.nsteps_run, wants_levels(io)).total) return -1;
     // checkpoints of a plan with mirror sides hold the ghosts that the
     // single-step kernels leave in the halo
     if (io.ckpt && p->mirror) return -1;
     // the kernels read and write whole 16-byte vectors
     for (const void *q : {static_cast<const void *>(io.field[0]), static_cast<const void *>(io.field[1]), scratch})
         if (reinterpret_cast<uintptr_t>(q) % 16) return -1;
-    for (int r = 0; r <= 3; ++r)
-        if (launches_for(io.nsteps_run - r, c.steps)) return r;
-    return -1;
+    return singles_of(io.nsteps_run, c.steps);
 }
 
 template <typename T>
@@ -113,7 +133,7 @@ sw_status enqueue_multi2d(const sw_plan *p, const Run2D<T> &io, int singles, voi
     constexpr bool f64 = std::is_same_v<T, double>;
     const Multi2DChoice choice = multi2d_choice(p);
     const Multi2DTile tile = multi2d_tile(choice.tile, int(sizeof(T)));
-    const ScratchMap map(p, choice.steps);
+    const ScratchMap map(p, choice.steps, io.nsteps_run, wants_levels(io));
     char *base = static_cast<char *>(scratch);
     auto buffer = [&](int k) { return reinterpret_cast<T *>(base + map.field * k); };
     T *inj = reinterpret_cast<T *>(base + map.inj);
@@ -160,7 +180,7 @@ sw_status enqueue_multi2d(const sw_plan *p, const Run2D<T> &io, int singles, voi
     const bool snaps = io.snaps && io.saving_stride > 0, ckpts = io.ckpt != nullptr;
     // whole buffers are copied into checkpoints, and their halo stays zero
     if (ckpts)
-        for (int k = 0; k < 2 + 2 * std::max(0, choice.steps - 2); ++k) {
+        for (int k = 0; k < 2 + 2 * map.between; ++k) {
             if constexpr (f64) SW_HIP(launch_fill64(buffer(k), p->field_elems, s));
             else SW_HIP(launch_fill(buffer(k), p->field_elems, 0.0f, s));
         }
@@ -178,7 +198,7 @@ sw_status enqueue_multi2d(const sw_plan *p, const Run2D<T> &io, int singles, voi
         P.out[nt - 1] = j % 2 ? io.field[last % 2] : buffer(0);
         P.out[nt - 2] = j % 2 ? io.field[(last + 1) % 2] : buffer(1);
         if (nrec || snaps || ckpts)
-            for (int k = 0; k < nt - 2; ++k) P.out[k] = buffer(2 + (j % 2) * (choice.steps - 2) + k);
+            for (int k = 0; k < nt - 2; ++k) P.out[k] = buffer(2 + (j % 2) * map.between + k);
         P.inj = inj + size_t(n - n0) * nuniq;
         P.tz = tile.ez - 2 * p->r * nt;
         P.ty = tile.ey - 2 * multi2d_pad_y(p->r * nt, int(sizeof(T)));

@@ -23,8 +23,12 @@ struct Run2D {
 // Tile and steps per launch of the plan (steps 0: the single-step kernels).
 Multi2DChoice multi2d_choice(const sw_plan *p);
 
-// Scratch bytes of a run of the plan's steps (0: the plan takes the single-step kernels).
-int64_t multi2d_scratch_bytes(const sw_plan *p);
+// Scratch bytes of a run of nsteps steps; levels: those between a launch's last
+// two are wanted (snapshots, checkpoints; receivers want them by themselves).
+// 0: the plan takes the single-step kernels.
+int64_t multi2d_scratch_bytes(const sw_plan *p, int nsteps, bool levels);
+// Whether a run of nsteps steps divides into launches of several.
+bool multi2d_divides(const sw_plan *p, int nsteps);
 
 // Steps at the start of the run that the single-step kernels take (the rest
 // divides into launches of several steps), or -1: all of them.

@@ -271,8 +271,8 @@ class Propagator:
         io.saving_stride = int(saving_stride)
         io.step0 = int(step0)
         io.nsteps_run = nrun
-        scratch = self._scratch(False)
-        self._keep = (wavelet, fields, traces, snaps, scratch)
+        scratch = self._scratch((nrun, bool(saving_stride), None))
+        self._keep = (wavelet, fields, traces, snaps)
         L.check("sw_forward_f64", L.lib().sw_forward_f64_scratch(
             self._plan, ctypes.byref(io), _ptr(scratch), scratch.numel() if scratch is not None else 0, _stream()))
         return ForwardResult(traces, fields, nrun % 2, snaps, None, 0)
@@ -339,14 +339,22 @@ class Propagator:
             self._field2 = (self.new_field(), self.new_field())
         return self._field2
 
-    def _scratch(self, graph):
-        """Device scratch of a forward, or None.  Launches (graph False) take one per
-        call, so that runs of one plan may overlap on several streams.  A graph is
-        replayed on the buffers it was captured with: its scratch is kept with the
-        wavefields that it writes (graph: the two buffers), and a graph over other
-        wavefields, which may overlap with it, gets another."""
-        n = ctypes.c_int64(0)
-        L.check("sw_plan_scratch", L.lib().sw_plan_scratch(self._plan, ctypes.byref(n)))
+    def _scratch(self, run):
+        """Device scratch of a forward, or None.  run: (steps, whether snapshots or
+        checkpoints are asked for, and for a graph the two wavefields it writes, else
+        None); False: as much as any run of the plan has a use for.
+
+        Launches take one per call, so that runs of one plan may overlap on several
+        streams; it goes back to the allocator when the call returns (whose work on
+        the stream comes before that of the next owner).  A graph is replayed on the
+        buffers it was captured with: its scratch is kept with the wavefields, and a
+        graph over others, which may overlap with it, gets another."""
+        n, graph = ctypes.c_int64(0), None
+        if run:
+            steps, levels, graph = run
+            L.check("sw_run_scratch", L.lib().sw_run_scratch(self._plan, steps, int(levels), ctypes.byref(n)))
+        else:
+            L.check("sw_plan_scratch", L.lib().sw_plan_scratch(self._plan, ctypes.byref(n)))
         if n.value == 0:
             return None
         key = tuple(f.data_ptr() for f in graph) + (n.value,) if graph else None
@@ -423,8 +431,8 @@ class Propagator:
         spare = self._spare_fields()
         if spare is not None:
             io.field2[0], io.field2[1] = spare[0].data_ptr(), spare[1].data_ptr()
-        scratch = self._scratch(fields if use_graph else False)
-        self._keep = (wavelet, fields, traces, snaps, ckpt, scratch)
+        scratch = self._scratch((nrun, bool(saving_stride or checkpoint_every), fields if use_graph else None))
+        self._keep = (wavelet, fields, traces, snaps, ckpt)
         L.check("sw_forward", L.lib().sw_forward_scratch(
             self._plan, ctypes.byref(io), _ptr(scratch), scratch.numel() if scratch is not None else 0, _stream()))
         return ForwardResult(traces, fields, nrun % 2, snaps, ckpt, int(checkpoint_every))

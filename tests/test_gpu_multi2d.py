@@ -78,3 +78,27 @@ def test_resume_and_buffers_off_16_bytes(monkeypatch):
     c, _ = _run(monkeypatch, True, *args, step0=6, offset=1)      # left to the single-step kernels
     for x, y, z in zip(a, b, c):
         assert torch.equal(x, y) and torch.equal(x, z)
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_runs_without_receivers_keep_only_the_levels_that_are_read(monkeypatch, dtype):
+    from paper_2201_05278_amd import Propagator, critical_dt, ricker
+    n, h, so, steps = (120, 170), (10.0, 12.5), 4, 29
+    dt = 0.7 * critical_dt(h, so, 3000.0)
+    wav = ricker(25.0, dt, steps).reshape(-1, 1)
+    for kw in ({}, {"saving_stride": 3}) + (({"checkpoint_every": 5}, {"saving_stride": 4, "checkpoint_every": 7})
+                                            if dtype == "float32" else ()):
+        print(f"case: 2D without receivers {dtype} {kw}", flush=True)
+        out = []
+        for multi in (True, False):
+            prop = Propagator(n, h, so, dt, steps, nbl=9, dtype=dtype)
+            prop.set_sources([[605.0, 1061.0]], "hicks")
+            prop.prepare(torch.full(n, 2500.0, dtype=prop.torch_dtype), cmax=3000.0)
+            if not multi:
+                monkeypatch.setattr(prop, "_scratch", lambda run: None)
+            assert prop.launch()["steps"] > 2
+            r = prop.forward(wav, **kw)
+            out.append([prop.grid_view(f) for f in r.fields] + [t for t in (r.snaps, r.ckpt) if t is not None])
+        assert float(out[0][0].abs().max()) > 0.0
+        for a, b in zip(*out):
+            assert torch.equal(a, b)

@@ -48,8 +48,36 @@ def test_graphs_over_other_wavefields_have_a_scratch_of_their_own(recorder):
     held = []                                    # as while both graphs are in flight: nothing is handed out twice
     for fields in (pairs[0], pairs[0], pairs[1]):
         prop.forward(wav, use_graph=True, fields=fields)
-        held.append(prop._keep)
+        held.append(prop._graph_scratch)
     (a, na), (b, nb), (c, nc) = recorder.calls
     assert a and na == nb == nc > 0
     assert a == b                                # a replay finds the scratch its graph was captured with
     assert c != a
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_a_run_asks_for_the_levels_it_needs_and_gives_them_back(recorder, dtype):
+    wav, sizes = torch.zeros(20, 1), {}
+    for receivers in (True, False):
+        prop = _prop(receivers=receivers, dtype=dtype)
+        steps, field = prop.launch()["steps"], prop.layout.field_elems * (4 if dtype == "float32" else 8)
+        assert steps > 2
+        for stride in (0, 5):
+            recorder.calls.clear()
+            prop.forward(wav, saving_stride=stride)
+            sizes[receivers, stride] = recorder.calls[0][1] // field
+            assert recorder.calls[0][0]
+            kept = [t for t in prop.__dict__.values() if isinstance(t, torch.Tensor)]
+            for item in prop._keep:
+                kept += item if isinstance(item, tuple) else [item]
+            assert not any(t is not None and t.dtype == torch.uint8 for t in kept)      # nothing holds the scratch
+    full = 2 + 2 * (steps - 2)
+    assert sizes == {(True, 0): full, (True, 5): full, (False, 5): full, (False, 0): 2}
+
+
+def test_a_run_too_short_for_a_launch_asks_for_nothing(recorder):
+    prop, wav = _prop(), torch.zeros(20, 1)
+    for steps in (1, 3, 4):
+        prop.forward(wav, step0=2, nsteps_run=steps)
+    assert [bool(p) for p, _ in recorder.calls] == [False, False, True]
+    assert recorder.calls[0][1] == 0
