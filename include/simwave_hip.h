@@ -433,6 +433,9 @@ sw_status sw_batch_destroy(sw_batch *batch);
  * list, -1 one block per tile, 0 the default (one block per tile for 3D
  * shots, 8 looping blocks per compute unit for 2D shots).  Plain tile
  * shapes only (wt 0, ts 1, occ 0; order is ignored; zc 0: the default chunk).
+ * The default 3D tile, (16, 4) with nt 1 and pf 1, runs 16-byte vectors of
+ * columns, also when it is set explicitly; every other one runs one column per
+ * thread.
  * Results do not depend on any of it. */
 sw_status sw_batch_set_tiling(sw_batch *batch, const sw_tiling *t, int32_t blocks_per_cu);
 sw_status sw_batch_get_tiling(const sw_batch *batch, sw_tiling *out, int32_t *blocks_per_cu);

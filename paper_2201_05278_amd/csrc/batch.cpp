@@ -124,7 +124,7 @@ sw_status batch_step(sw_batch *b, void *table, int k, bool points, hipStream_t s
     const auto *tiles = reinterpret_cast<const int *>(t + b->off_tiles);
     const auto *pts = reinterpret_cast<const ShotPoints *>(t + b->off_points);
     const Tiling &bt = b->tiling;
-    if (b->ndim == 3 && bt.tx == 16 && bt.nw == 4 && bt.nt == 1 && bt.pf == 1)
+    if (batch_vectors(b->ndim, bt.tx, bt.nw, bt.nt, bt.pf))
         SW_HIP(launch_vec_batch(b->r, params, tiles, b->nshots, k % 2, persistent_blocks(b), s));
     else
         SW_HIP(launch_const_batch(b->r, b->ndim, bt, params, tiles, b->nshots, k % 2, persistent_blocks(b), s));

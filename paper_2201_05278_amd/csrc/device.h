@@ -194,6 +194,15 @@ struct ShotPoints {
     float *traces;
 };
 
+// Whether a batch tiling runs 16-byte vectors of columns (k_vec_batch): 3D blocks
+// of 16 rows and 4 waves, streamed, one plane ahead, which own the same 16 x 64
+// nodes either way.  Twelve shots of 150 .. 260 nodes per side, ms per step on
+// vectors and one column per thread: SO2 0.649 0.693, SO8 0.700 0.804, SO12 0.713
+// 0.821, SO16 0.714 1.168, SO20 0.822 1.294 (every order gains).
+constexpr bool batch_vectors(int ndim, int tx, int nw, int nt, int pf)
+{
+    return ndim == 3 && tx == 16 && nw == 4 && nt == 1 && pf == 1;
+}
 hipError_t launch_const_batch(int r, int ndim, const Tiling &t, const StencilParams *shots,
                               const int *tile_start, int nshots, int parity, int nblocks,
                               hipStream_t s);

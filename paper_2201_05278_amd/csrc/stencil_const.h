@@ -680,11 +680,12 @@ hipError_t launch_batch_v(int ndim, const Tiling &t, const StencilParams *shots,
         return hipGetLastError();
     }
 #define SW_X(TXV, NWV)                                                                               \
-    if (t.tx == TXV && t.nw == NWV) {                                                                \
-        hipLaunchKernelGGL((k_const_batch<R, 3, TXV, NWV, NT, PF>), dim3(nblocks), dim3(64 * NWV), 0, s, \
-                           shots, tile_start, nshots, parity);                                       \
-        return hipGetLastError();                                                                    \
-    }
+    if constexpr (!batch_vectors(3, TXV, NWV, NT, PF))                                                \
+        if (t.tx == TXV && t.nw == NWV) {                                                            \
+            hipLaunchKernelGGL((k_const_batch<R, 3, TXV, NWV, NT, PF>), dim3(nblocks), dim3(64 * NWV), 0, s, \
+                               shots, tile_start, nshots, parity);                                   \
+            return hipGetLastError();                                                                \
+        }
     SW_CONST_SHAPES(SW_X)
 #undef SW_X
     return hipErrorInvalidValue;

@@ -206,3 +206,16 @@ def test_the_search_for_a_launch_runs_once_per_plan():
         assert prop.launch() == first
         times.append(time.perf_counter() - t)
     assert first["kind"] == "vector" and min(times) < 1e-3
+
+
+@pytest.mark.parametrize("so", range(2, 21, 2))
+def test_every_batch_tile_is_bitwise_the_single_shots(so):
+    from paper_2201_05278_amd import Batch
+    print(f"case: batch tiles SO{so}", flush=True)
+    sets = [_prop(n, so, 6, 3) for n in ((25, 40, 71), (31, 22, 130))]
+    ref = [p.forward(w).traces.clone() for p, w in sets]
+    batch = Batch([p for p, _ in sets])
+    for tile in (None, (16, 4, 9), (16, 4, 9, 0), (16, 4, 9, 1, 2), (8, 4, 7), (24, 8), (32, 8, 11, 0, 2)):
+        batch.set_tiling(*tile) if tile else batch.set_tiling()
+        for a, b in zip(batch.forward([w for _, w in sets]), ref):
+            assert float(b.abs().max()) > 0.0 and torch.equal(a, b), tile
