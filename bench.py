@@ -43,9 +43,14 @@ METRIC = "Gpts/s (grid updates/s) fwd and fwd+adjoint, 3D 512^3 SO8 FP32; % HBM 
 # HBM bytes per launch of the dominant kernel from the counter runs recorded in
 # profiles/stencil_const_smooth3d_592_traffic.md (FETCH_SIZE x 2.000 and
 # WRITE_SIZE x 1.000, both calibrated on a 1 GiB copy), valid only for the
-# configuration that was profiled: the default tiling, whose launches run vector tiles.
-PROFILED = {"tiling": {"tx": 24, "nw": 8, "zc": 74, "nt": 1, "pf": 1, "wt": 0, "ts": 1, "occ": 0, "order": 1},
+# launch that was profiled: vector tiles of 24 x 128 columns in chunks of 296 planes.
+PROFILED = {"launch": {"kind": "vector", "tile": 7, "rows": 24, "cols": 128, "zc": 296, "steps": 1},
             "n": 512, "bytes": (1340819.4 * 2.000 + 810448.0 * 1.000) * 1024}
+
+
+def profiled_bytes(launch, n):
+    """Recorded HBM bytes of a launch on the n^3 workload, None if another one was profiled."""
+    return PROFILED["bytes"] if launch == PROFILED["launch"] and n == PROFILED["n"] else None
 
 
 def log(msg):
@@ -193,8 +198,8 @@ def paper_shapes(dtypes=("float32", "float64")):
                 prop.prepare(torch.from_numpy(wl.vel).to(tdt).cuda(), cmax=cmax)
                 wav = ricker(wl.f_peak, dt, nt).reshape(-1, 1).to(tdt).cuda()
                 if wl.ndim == 3 and dtype == "float32":
-                    # the library's own tiling search for this grid (2D runs are bound by
-                    # launch latency, which its per-launch timing does not see)
+                    # the library's own tiling search for this grid (in 2D it times single
+                    # steps, which these runs do not take)
                     prop.autotune()
                 fields = (prop.new_field(), prop.new_field())
                 traces = torch.zeros((nt, len(wl.rec)), dtype=tdt, device="cuda")
@@ -210,7 +215,7 @@ def paper_shapes(dtypes=("float32", "float64")):
                                   "steps": nt, "boundary": wl.bc, "seconds": round(el, 4),
                                   "gpts": round(nodes * nt / el / 1e9, 2), "paper_best_seconds": paper_s,
                                   "paper_best_gpts": round(nodes * nt / paper_s / 1e9, 3),
-                                  "tiling": prop.tiling}), flush=True)
+                                  "launch": prop.launch()}), flush=True)
                 del prop, fields, traces
                 torch.cuda.empty_cache()
 
@@ -299,8 +304,8 @@ def main():
     achieved = nodes * BYTES_PER_NODE["const"] / (avg_ms * 1e-3) / 1e9
     out["forward"] = gpts
     out["stencil_ms"] = avg_ms
-    tiling = prop.tiling
-    traffic = PROFILED["bytes"] if (tiling == PROFILED["tiling"] and args.n == PROFILED["n"]) else None
+    launch = prop.launch()
+    traffic = profiled_bytes(launch, args.n)
     log(f"bench: forward {gpts:.1f} Gpts/s, stencil {avg_ms:.3f} ms -> {achieved:.0f} GB/s")
     del prop
     torch.cuda.empty_cache()
@@ -380,7 +385,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": None if traffic is None else round(traffic / 1e9, 4),
-                     "traffic_unit": "GB per launch", "tiling": tiling,
+                     "traffic_unit": "GB per launch", "launch": launch,
                      "kernel": "constant-density stencil, 16 B/node x nodes per launch",
                      "avg_launch_ms": round(avg_ms, 4)},
         "cpu_baseline": cpu,

@@ -96,3 +96,13 @@ def test_2d_tiles_follow_the_compute_units():
     search = getattr(L.lib(), "_ZN2sw14choose_multi2dEiiiii")          # radius, bytes per value, extents, compute units
     search.restype, search.argtypes = Choice, [ctypes.c_int] * 5
     assert search(4, 4, 281, 281, 64).steps < search(4, 4, 281, 281, 256).steps      # tiles queue: less halo per launch
+
+
+def test_the_benchmark_reports_traffic_of_the_launch_that_was_profiled():
+    import bench
+    assert bench.profiled_bytes(bench.PROFILED["launch"], 512) == bench.PROFILED["bytes"]
+    prop = _plan((512, 512, 512), 8)
+    prop.set_launch(bench.PROFILED["launch"]["tile"], bench.PROFILED["launch"]["zc"])
+    assert bench.profiled_bytes(prop.launch(), 512) == bench.PROFILED["bytes"]
+    prop.set_tiling(24, 8, 74)                  # scalar tiles that move other bytes
+    assert bench.profiled_bytes(prop.launch(), 512) is None
