@@ -131,13 +131,15 @@ namespace {
 // SO8, every side mirrored: one round 0.730 ms, 8 chunks of 74 planes 0.677),
 // and the other waves of a SIMD must fill the wait at their second barrier.  So
 // their own constants (fitted to 350 grids of 0.3 M .. 250 M nodes in single
-// precision up to SO18 and 66 in double at SO2 and SO4, every tile and 14 chunk
+// precision up to SO18 and 300 in double at SO2 and SO4, every tile and 14 chunk
 // counts each) charge a plane by the waves it leaves per SIMD (qw), more where
 // those differ between SIMDs (uneven), and favour at equal waits a tile that has
 // the CU to itself (ql).  Choices ran 3.0% behind the sweep's best on average,
 // 17% at worst (with the constants above 17% and 130%).  Of 1300 other grids six
 // ran more than 1.5% behind the scalar tiles, 8% at worst (67 of 366 with the
 // constants above, 25%: 768 x 532 x 507 SO18, 1373 us against 1041, now 958).
+// In doubles 3.6% on average, 16% at worst (9.5% and 54%), no grid behind the
+// scalar tiles.
 // In doubles from SO6 on the general constants hold, with tiles of which two
 // fit and whose waves spread evenly over the SIMDs (207 x 801 x 801 SO8: 24 x 64
 // 0.957 ms, 16 x 64 0.861).  Imaging launches, with up to seven streams, want the
@@ -148,7 +150,7 @@ struct CostModel {
 constexpr CostModel kCost32{4.07e-4, 6.3e-7, 0.061, 1.3, 0.17, 0.25, 1.8, 0.075, 1.21, 1.35, 0.02, 1.55, 1.5, 0.0, 1.0, 1.0};
 constexpr CostModel kCost64{5.08e-4, 0.0, 0.084, 1.8, 0.24, 0.11, 1.0, 0.26, 1.03, 1.54, 0.02, 0.21, 1.15, 0.0, 1.0, 1.0};
 constexpr CostModel kMirror32{4.07e-4, 3.1e-7, 0.0088, 1.19, 0.366, 0.128, 1.68, 0.145, 1.205, 2.06, 0.052, 0.656, 1.254, 0.163, 1.276, 0.978};
-constexpr CostModel kMirror64{2.82e-4, 0.0, 0.0334, 0.32, 0.239, 0.165, 1.04, 0.278, 1.09, 0.964, 0.0692, 0.706, 0.989, 1.18, 1.04, 0.98};
+constexpr CostModel kMirror64{3.51e-4, 0.0, 0.0604, 0.112, 0.151, 0.207, 1.016, 0.281, 1.09, 1.445, 0.0646, 0.55, 1.099, 1.016, 1.461, 0.98};
 
 template <typename T>
 VecChoice choose(const sw_plan *p, int mode)

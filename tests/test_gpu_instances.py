@@ -175,7 +175,8 @@ ALL = (("neumann", "dirichlet"), ("dirichlet", "dirichlet"), ("dirichlet", "diri
     ((438, 574, 369), 18, "float32", ALL, ("vector", 24, 128)),     # 437, 623, 511
     ((466, 495, 397), 20, "float32", ALL, ("block", 8, 64)),        # 558, 671, 557
     ((138, 179, 137), 20, "float32", ALL, ("vector", 16, 64)),      # 45, 54, 78
-    ((178, 325, 319), 2, "float64", ALL, ("vector", 8, 64)),        # 100, 131, 110
+    ((178, 325, 319), 2, "float64", ALL, ("vector", 12, 128)),      # 106, 131, 110
+    ((207, 801, 801), 2, "float64", ALL, ("vector", 12, 128)),      # 853, 885, -
     ((713, 601, 378), 2, "float32", None, ("block", 8, 64)),        # 499, 528, 492
     ((592, 592, 592), 8, "float32", None, ("vector", 24, 128)),     # 618, -, 649
 ])
