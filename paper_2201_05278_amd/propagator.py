@@ -349,6 +349,8 @@ class Propagator:
         the stream comes before that of the next owner).  A graph is replayed on the
         buffers it was captured with: its scratch is kept with the wavefields, and a
         graph over others, which may overlap with it, gets another."""
+        if self.ndim != 2 or self.scheme != "const":
+            return None                         # (no plan of these asks for any)
         n, graph = ctypes.c_int64(0), None
         if run:
             steps, levels, graph = run
