@@ -47,7 +47,8 @@
  *     origin + (i0 * padded[1] + i1) * padded[2] + i2          (3D)
  *     origin + i0 * padded[1] + i1                             (2D)
  * The halo around the extended grid is stored and must stay zero in
- * wavefield buffers (the library never writes it after clearing the buffer).
+ * wavefield buffers (the library clears it with the buffer and then writes
+ * nothing to it but zeros, and on mirrored sides their ghosts).
  * Interior rows start on 256-byte boundaries if the buffer base is 256-byte
  * aligned.
  */
@@ -340,7 +341,7 @@ sw_status sw_adjoint(sw_plan *plan, const sw_adj_io *io, void *stream);
 /* Stencil tiling of a plan.  Results never depend on it.  A 3D plan whose
  * tiling is left at the defaults runs vector tiles where those are faster (16
  * bytes of columns per thread; tile and z chunk from a cost model of the
- * launch); any field set here makes it run the tiles described below.  A 2D
+ * launch; sw_plan_get_launch reports them); any field set here makes it run the tiles described below.  A 2D
  * plan likewise runs single steps, with or without scratch, once a field is set.
  *   tx, nw  rows per block and waves per block.  3D constant density:
  *           block tiles (16,4), (8,4), (32,8), (16,8), (8,8), (24,8), or with wt = 1
@@ -411,9 +412,9 @@ sw_status sw_plan_set_launch(sw_plan *plan, int32_t role, int32_t tile, int32_t 
  * waves per launch, chunks of at most 74 planes. */
 sw_status sw_plan_get_tiling(const sw_plan *plan, sw_tiling *out);
 /* Resident blocks per compute unit of the plan's block-tile kernel under its
- * current tiling, as sw_plan_get_tiling reports it (the runtime's occupancy calculator) and the device's
- * compute units: set for 3D block tiles (every scheme and precision), 0
- * and 0 otherwise or without a device. */
+ * current tiling, as sw_plan_get_tiling reports it (the runtime's occupancy
+ * calculator), and the device's compute units: set for 3D block tiles (every
+ * scheme and precision), 0 and 0 otherwise or without a device. */
 sw_status sw_plan_occupancy(const sw_plan *plan, int32_t *blocks_per_cu, int32_t *cus);
 
 /* ---- batched shots and autotuning --------------------------------------- */
@@ -468,17 +469,19 @@ sw_status sw_batch_forward(sw_batch *batch, const sw_batch_io *io, void *stream)
  * serialised by the caller.  Results are bitwise those of sw_batch_forward. */
 sw_status sw_batch_forward_static(sw_batch *batch, const sw_batch_io *io, void *stream);
 
-/* Pick the library's default (3D: vector tiles), or the tile shape (rows per tile, waves per block), the z-chunk length,
- * cache policy and prefetch depth, for single plans also the two-step sweep
- * (when io->field2 is given) and a cap of 4 resident blocks per CU, and (for
- * batches) the launch grid (one block per tile or a looping grid), by timing a few steps of each
- * candidate on the given buffers (their contents are overwritten), or reuse
- * the choice stored under the same problem key in the JSON file `cache_path`
- * (may be NULL: no cache).  Candidates of a plan are timed as single forward steps:
- * its choice holds for those (also in the adjoint), while recompute and imaging
- * launches, and 2D launches of several steps, stay the library's.  The choice is kept in the plan / batch and
- * written back to the cache; an entry written by a library with other kernels
- * is tuned again.  Synchronises `stream`. */
+/* Pick the library's default (3D: vector tiles), or the tile shape (rows per
+ * tile, waves per block), the z-chunk length, cache policy and prefetch depth,
+ * for single plans also the two-step sweep (when io->field2 is given) and a cap
+ * of 4 resident blocks per CU, and (for batches) the launch grid (one block per
+ * tile or a looping grid), by timing a few steps of each candidate, with the
+ * ghost fill that it needs, on the given buffers (their contents are
+ * overwritten), or reuse the choice stored under the same problem key in the
+ * JSON file `cache_path` (may be NULL: no cache).  Candidates of a plan are timed
+ * as single forward steps: its choice holds for those (also in the adjoint),
+ * while recompute and imaging launches, and 2D launches of several steps, stay
+ * the library's.  The choice is kept in the plan / batch and written back to the
+ * cache; an entry written by a library with other kernels is tuned again.
+ * Synchronises `stream`. */
 sw_status sw_plan_autotune(sw_plan *plan, const sw_fwd_io *io, const char *cache_path, void *stream);
 sw_status sw_batch_autotune(sw_batch *batch, const sw_batch_io *io, const char *cache_path,
                             void *stream);

@@ -11,9 +11,10 @@
 // What bounds them: instructions.  Staggered, 592^3 SO8: 113 vector instructions
 // per node keep the SIMDs 45% busy and LDS 31%, in phases that a block's barriers
 // keep apart, 1.318 ms per step (scalar tiles 1.361; 20 bytes per node at the
-// card's rate take 0.74); 240^3 104 against 122 us.  Centred, 280^3 SO8: 98 per
-// node, three quarters of the issue slots of a SIMD that holds two waves, 130
-// against 156 us.
+// card's rate take 0.74); 240^3 104 against 122 us.  Centred, 280^3 SO8: 103 per
+// node, in half of the cycles of SIMDs that hold two waves, LDS 34% (three fifths
+// of that bank conflicts of the 32-column tile's rows), 4.4 TB/s with the halo
+// re-reads; 132 against 156 us.
 // CW is 4 up to R = 4 (staggered) and R = 6 (centred), else 2: three (two)
 // queues of 2R vectors of 4 would not leave two waves per SIMD their registers
 // (two columns per thread at R = 4, held to four waves, ran no faster: centred

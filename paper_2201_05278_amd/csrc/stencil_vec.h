@@ -13,7 +13,10 @@
 // What bounds it: HBM at the larger sizes (592^3 SO8, 3 reads and 1 write per
 // node: 0.614 ms, 5.4 TB/s, where the scalar tiles take 0.69), the chain of
 // loads, barrier and LDS reads per plane where a launch is one round (128^3 with
-// its layer 14 against 20 us), and FMAs from SO16 on (336^3: 154 against 222 us).
+// its layer 14 against 20 us).  High orders at sizes between have no one limit:
+// 336^3 SO16 (149 us, scalar tiles 222) moves 5.15 TB/s with the halo re-reads
+// (reads 1.35 of the algorithmic bytes), its SIMDs issue vector instructions in
+// 54% of the cycles and LDS is busy in 21%.
 // Mirror ghosts are made in LDS (x, y) and by the plane that is loaded (z), so
 // that no ghost fill runs before the sweep (53 us of 960 us per step at
 // 207 x 801 x 801 in double precision).
