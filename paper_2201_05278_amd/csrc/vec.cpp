@@ -390,7 +390,8 @@ static VecChoice search_vec(const sw_plan *p, int mode, bool &searched)
 
 VecChoice choose_vec(const sw_plan *p, int mode)
 {
-    if (p->ndim != 3 || !library_picks(p, mode) || (p->mirror && mode != MODE_FWD)) return {};
+    const bool forward_only = p->mirror || p->prob.dtype == SW_F64 || p->prob.scheme == SW_VD_CENTRED;   // (no adjoint)
+    if (p->ndim != 3 || !library_picks(p, mode) || (forward_only && mode != MODE_FWD)) return {};
     const bool mirror = p->prob.scheme == SW_CONST && p->mirror;
     if (const sw_plan::Pin &pin = p->pin[mode]; pin.tile >= 0) return {pin.tile, std::min(pin.extent, p->dims[0]), mirror};
     uint64_t v = p->choice[mode].load(std::memory_order_relaxed);

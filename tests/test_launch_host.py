@@ -37,6 +37,13 @@ def test_vector_tiles_of_every_scheme_and_role():
     assert _tiles(_plan(n, 20, "vd_centred")) == [0, 1, 3] and _tiles(_plan(n, 8, "vd_centred"), "recompute") == []
 
 
+def test_plans_without_an_adjoint_have_no_vector_tiles_for_it():
+    n = (40, 44, 48)
+    for prop in (_plan(n, 8, "vd_centred"), _plan(n, 8, dtype="float64"), _plan(n, 8, "vd_staggered", bc=(("none", "neumann"),) * 3)):
+        assert all(prop.launch(role)["kind"] == "block" for role in ("recompute", "image", "image_pair"))
+    assert _plan(n, 8, "vd_staggered").launch("recompute")["kind"] == "vector"
+
+
 def test_a_launch_is_refused_or_taken_back():
     prop = _plan((40, 44, 48), 8)
     own = prop.launch()
