@@ -119,7 +119,7 @@ int compute_units(const sw_plan *p)
                   hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
                      ? n
                      : -1;
-    return p->ncu > 0 ? p->ncu : 256;
+    return p->ncu > 0 ? p->ncu.load() : 256;
 }
 
 // Resident blocks per CU of the plan's 3D forward kernel for tiling t
@@ -129,6 +129,7 @@ int resident_blocks(const sw_plan *p, const Tiling &t)
     const uint64_t key = (uint64_t(t.tx) << 40) | (uint64_t(t.nw) << 32) | (uint64_t(t.nt) << 24) |
                          (uint64_t(t.pf) << 16) | (uint64_t(t.wt) << 12) | (uint64_t(t.ts) << 8) |
                          uint64_t(t.occ & 0xff);
+    const std::lock_guard<std::mutex> lock(p->resident_lock);
     for (const auto &e : p->resident_cache)
         if (e.first == key) return e.second;
     (void)compute_units(p);

@@ -4,6 +4,7 @@
 
 #include <atomic>
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -107,9 +108,11 @@ struct sw_plan {
     // (point tables and counts, model, tiling); part of the graph keys
     uint64_t generation = 1;
     // resident blocks per CU of the constant-density block-tile kernels, by
-    // tiling key (queried once per kernel), and the device's CU count
+    // tiling key (queried once per kernel; behind a lock, since calls on one plan
+    // may come from several threads), and the device's CU count
     mutable std::vector<std::pair<uint64_t, int>> resident_cache;
-    mutable int ncu = 0;
+    mutable std::mutex resident_lock;
+    mutable std::atomic<int> ncu{0};
     // the library's vector tile and chunk per mode, or 2D tile and step count
     // (packed by Choice; 0: not searched for yet), which the plan's problem fixes
     mutable std::atomic<uint64_t> choice[4] = {};

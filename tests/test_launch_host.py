@@ -113,3 +113,14 @@ def test_the_benchmark_reports_traffic_of_the_launch_that_was_profiled():
     assert bench.profiled_bytes(prop.launch(), 512) == bench.PROFILED["bytes"]
     prop.set_tiling(24, 8, 74)                  # scalar tiles that move other bytes
     assert bench.profiled_bytes(prop.launch(), 512) is None
+
+
+def test_threads_share_a_plan():
+    """Threads that ask one plan for its tilings (each of them caches occupancies in it) agree with a plan asked alone."""
+    from concurrent.futures import ThreadPoolExecutor
+    for scheme in ("const", "vd_staggered", "vd_centred"):
+        alone, shared = _plan((90, 70, 80), 12, scheme), _plan((90, 70, 80), 12, scheme)
+        want = (alone.tiling, alone.launch())
+        with ThreadPoolExecutor(8) as pool:
+            got = list(pool.map(lambda _: (shared.tiling, shared.launch()), range(64)))
+        assert all(g == want for g in got)
