@@ -304,12 +304,14 @@ double vd_scalar_cost(const sw_plan *p)
 // last round, by more than the kernels differ at some orders (staggered SO12,
 // 340^3 503 against 425 us but 440^3 887 against 957).  So the two costs decide:
 // vector tiles run where the scalar cost is above the mean (geometric) of the
-// vector cost and the ideal by the order's factor.  Of 276 other grids this left
-// 3 more than 1.5% slower than the scalar tiles, 5% at worst (a rule by size alone
-// 59 of 1229, 9%).  At the other orders vector tiles run throughout: staggered SO8
-// (6 of 113 slower, 7% at worst; 592^3 1287 against 1349 us) and SO16 (none of 31,
-// 1.52 times as fast on average), centred SO6 .. SO14, SO18 and SO20 (1 of 242, 4%;
-// 1.2 times as fast and more on average).
+// vector cost and the ideal by the order's factor, centred SO2 up to 40 M nodes
+// only (above, five of seven grids where the costs chose vector tiles lost 2 to 5%
+// by them).  Of 489 other grids this left 2 more than 1.5% slower than the scalar
+// tiles, 2% at worst (a rule by size alone 59 of 1229, 9%).  At the other orders
+// vector tiles run throughout: staggered SO8 (11 of 214 slower, 7% at worst; 592^3
+// 1287 against 1349 us) and SO16 (1 of 55, 3%; 1.5 times as fast on average),
+// centred SO6 .. SO14, SO18 and SO20 (3 of 418, 4%; 1.2 times as fast and more on
+// average).
 bool vd_vectors(const sw_plan *p, int mode, double cost)
 {
     const bool stag = p->prob.scheme == SW_VD_STAGGERED;
@@ -320,7 +322,8 @@ bool vd_vectors(const sw_plan *p, int mode, double cost)
     const double factor = stag ? kStag[p->r] : kCent[p->r];
     const double scalar = factor > 0.0 ? vd_scalar_cost(p) : 0.0;
     if (scalar <= 0.0) return true;
-    const double ideal = double(p->dims[0]) * p->dims[1] * p->dims[2] / compute_units(p);
+    const double nodes = double(p->dims[0]) * p->dims[1] * p->dims[2], ideal = nodes / compute_units(p);
+    if (!stag && p->r == 1 && nodes > 40e6) return false;
     return scalar > factor * std::sqrt(cost * ideal);
 }
 

@@ -192,6 +192,7 @@ def test_constant_density_choices(n, so, dtype, bc, want):
     ((359, 324, 256), 14, "vd_centred", ("vector", 8, 64)),         # 214, 274, 253
     ((328, 433, 436), 6, "vd_centred", ("vector", 8, 64)),          # 287, 334, 315
     ((280, 280, 280), 8, "vd_centred", ("vector", 32, 32)),         # 122, -, 148
+    ((510, 311, 457), 2, "vd_centred", ("block", 8, 64)),           # 307, 323, 307
 ])
 def test_variable_density_choices(n, so, scheme, want):
     assert _choice(n, so, scheme, "float32", None) == want
