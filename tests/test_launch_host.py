@@ -124,3 +124,18 @@ def test_threads_share_a_plan():
         with ThreadPoolExecutor(8) as pool:
             got = list(pool.map(lambda _: (shared.tiling, shared.launch()), range(64)))
         assert all(g == want for g in got)
+
+
+@pytest.mark.parametrize("n,so,dtype,kind", [
+    ((4010, 4030), 8, "float64", "block"),
+    ((4010, 4030), 10, "float64", "block"),         # single steps are 1.2 to 1.35 times as fast
+    ((2000, 2000), 10, "float64", "steps"),
+    ((1100, 1130), 12, "float64", "block"),
+    ((750, 1030), 12, "float64", "steps"),
+    ((720, 710), 14, "float64", "block"),
+    ((500, 500), 14, "float64", "steps"),
+    ((979, 1954), 20, "float32", "block"),
+    ((900, 900), 20, "float32", "steps"),
+])
+def test_2d_grids_that_take_single_steps(n, so, dtype, kind):
+    assert _plan(n, so, dtype=dtype).launch()["kind"] == kind
