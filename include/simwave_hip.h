@@ -244,9 +244,10 @@ sw_status sw_forward(sw_plan *plan, const sw_fwd_io *io, void *stream);
  * Depends on the grid, the step count, the sources and the tiling. */
 sw_status sw_plan_scratch(const sw_plan *plan, int64_t *bytes);
 /* The bytes that one run of nsteps_run steps has a use for, at most those of
- * sw_plan_scratch: without receivers, and with levels 0 (no snapshots or
- * checkpoints), two wavefields in place of up to 14; 0 for a run too short to
- * take several steps per launch. */
+ * sw_plan_scratch.  levels: 1 for snapshots plus 2 for checkpoints; with 0 and
+ * without receivers, two wavefields in place of up to 14.  0 bytes for a run too
+ * short to take several steps per launch, and for checkpoints of a plan with
+ * mirror sides, which take single steps. */
 sw_status sw_run_scratch(const sw_plan *plan, int32_t nsteps_run, int32_t levels, int64_t *bytes);
 
 /* sw_forward with `scratch_bytes` bytes of caller-owned device memory at

@@ -1014,7 +1014,7 @@ sw_status sw_run_scratch(const sw_plan *p, int32_t nsteps_run, int32_t levels, i
 {
     set_error("");
     if (!p || !bytes) return fail(SW_ERR_ARG, "NULL argument");
-    *bytes = multi2d_divides(p, nsteps_run) ? multi2d_scratch_bytes(p, nsteps_run, levels != 0) : 0;
+    *bytes = multi2d_divides(p, nsteps_run, levels & 2) ? multi2d_scratch_bytes(p, nsteps_run, levels != 0) : 0;
     return SW_OK;
 }
 

@@ -107,10 +107,14 @@ static int singles_of(int nsteps, int steps)
     return -1;
 }
 
-bool multi2d_divides(const sw_plan *p, int nsteps)
+// Checkpoints of a plan with mirror sides hold the ghosts that the single-step
+// kernels leave in the halo.
+static bool checkpoints_need_singles(const sw_plan *p) { return p->mirror; }
+
+bool multi2d_divides(const sw_plan *p, int nsteps, bool ckpt)
 {
     const Multi2DChoice c = multi2d_choice(p);
-    return c.steps && singles_of(nsteps, c.steps) >= 0;
+    return c.steps && !(ckpt && checkpoints_need_singles(p)) && singles_of(nsteps, c.steps) >= 0;
 }
 
 template <typename T>
@@ -118,9 +122,7 @@ int multi2d_singles(const sw_plan *p, const Run2D<T> &io, const void *scratch, i
 {
     const Multi2DChoice c = multi2d_choice(p);
     if (!c.steps || !scratch || bytes < ScratchMap(p, c.steps, io.nsteps_run, wants_levels(io)).total) return -1;
-    // checkpoints of a plan with mirror sides hold the ghosts that the
-    // single-step kernels leave in the halo
-    if (io.ckpt && p->mirror) return -1;
+    if (io.ckpt && checkpoints_need_singles(p)) return -1;
     // the kernels read and write whole 16-byte vectors
     for (const void *q : {static_cast<const void *>(io.field[0]), static_cast<const void *>(io.field[1]), scratch})
         if (reinterpret_cast<uintptr_t>(q) % 16) return -1;

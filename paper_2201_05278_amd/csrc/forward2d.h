@@ -27,8 +27,9 @@ Multi2DChoice multi2d_choice(const sw_plan *p);
 // two are wanted (snapshots, checkpoints; receivers want them by themselves).
 // 0: the plan takes the single-step kernels.
 int64_t multi2d_scratch_bytes(const sw_plan *p, int nsteps, bool levels);
-// Whether a run of nsteps steps divides into launches of several.
-bool multi2d_divides(const sw_plan *p, int nsteps);
+// Whether a run of nsteps steps, with checkpoints or without, divides into
+// launches of several.
+bool multi2d_divides(const sw_plan *p, int nsteps, bool ckpt);
 
 // Steps at the start of the run that the single-step kernels take (the rest
 // divides into launches of several steps), or -1: all of them.

@@ -340,8 +340,8 @@ class Propagator:
         return self._field2
 
     def _scratch(self, run):
-        """Device scratch of a forward, or None.  run: (steps, whether snapshots or
-        checkpoints are asked for, and for a graph the two wavefields it writes, else
+        """Device scratch of a forward, or None.  run: (steps, 1 for snapshots plus 2
+        for checkpoints, and for a graph the two wavefields it writes, else
         None); False: as much as any run of the plan has a use for.
 
         Launches take one per call, so that runs of one plan may overlap on several
@@ -354,7 +354,7 @@ class Propagator:
         n, graph = ctypes.c_int64(0), None
         if run:
             steps, levels, graph = run
-            L.check("sw_run_scratch", L.lib().sw_run_scratch(self._plan, steps, int(levels), ctypes.byref(n)))
+            L.check("sw_run_scratch", L.lib().sw_run_scratch(self._plan, steps, levels, ctypes.byref(n)))
         else:
             L.check("sw_plan_scratch", L.lib().sw_plan_scratch(self._plan, ctypes.byref(n)))
         if n.value == 0:
@@ -433,7 +433,7 @@ class Propagator:
         spare = self._spare_fields()
         if spare is not None:
             io.field2[0], io.field2[1] = spare[0].data_ptr(), spare[1].data_ptr()
-        scratch = self._scratch((nrun, bool(saving_stride or checkpoint_every), fields if use_graph else None))
+        scratch = self._scratch((nrun, bool(saving_stride) + 2 * bool(checkpoint_every), fields if use_graph else None))
         self._keep = (wavelet, fields, traces, snaps, ckpt)
         L.check("sw_forward", L.lib().sw_forward_scratch(
             self._plan, ctypes.byref(io), _ptr(scratch), scratch.numel() if scratch is not None else 0, _stream()))

@@ -33,8 +33,8 @@ def recorder(monkeypatch):
     return rec
 
 
-def _prop(n=(60, 80), so=8, receivers=True, dtype="float32"):
-    prop = Propagator(n, (10.0, 10.0), so, 1e-4, 20, nbl=8, device="cpu", dtype=dtype)
+def _prop(n=(60, 80), so=8, receivers=True, dtype="float32", **kw):
+    prop = Propagator(n, (10.0, 10.0), so, 1e-4, 20, nbl=8, device="cpu", dtype=dtype, **kw)
     prop.set_sources([[300.0, 400.0]], "linear")
     if receivers:
         prop.set_receivers([[100.0, 100.0]], "linear")
@@ -81,3 +81,11 @@ def test_a_run_too_short_for_a_launch_asks_for_nothing(recorder):
         prop.forward(wav, step0=2, nsteps_run=steps)
     assert [bool(p) for p, _ in recorder.calls] == [False, False, True]
     assert recorder.calls[0][1] == 0
+
+
+@pytest.mark.parametrize("side,wants", [("none", True), ("neumann", False), ("dirichlet", False)])
+def test_checkpoints_that_need_single_steps_ask_for_nothing(recorder, side, wants):
+    prop, wav = _prop(bc=[(side, "none"), ("none", "none")]), torch.zeros(20, 1)
+    prop.forward(wav, checkpoint_every=5)
+    prop.forward(wav, saving_stride=5)
+    assert [bool(p) for p, _ in recorder.calls] == [wants, True]
