@@ -367,8 +367,9 @@ hipError_t launch_radius(int tile, Multi2DParams<T> &P, hipStream_t s)
 // single ones: SO20 1.05 at 1.52 M nodes and 0.93 at 1.94 M; in doubles SO6
 // 1.09 at 13.1 M and 0.95 at 18.6 M, SO8 1.14 at 11.9 M and 0.96 at 16.7 M,
 // SO10 1.07 at 9.7 M and 0.87 at 12.5 M, SO12 1.08 at 1.0 M and 0.88 at
-// 1.24 M, SO14 1.13 at 0.27 M and 0.88 at 0.41 M.  Below the limits one grid of
-// 3700 was more than 1% slower than with single steps (SO12, 23.5 M: 0.988).
+// 1.24 M, SO14 1.13 at 0.27 M and 0.88 at 0.41 M.  Of 2700 grids
+// that still take several steps one is more than 1% slower than with single
+// steps (SO12, 23.5 M: 0.988).
 Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y, int cus)
 {
     Multi2DChoice best{};
