@@ -359,22 +359,24 @@ hipError_t launch_radius(int tile, Multi2DParams<T> &P, hipStream_t s)
 // measured 8.5 us + 1.75 us R, plus about 4e-6 us per node and 4 bytes; where
 // the model with a quarter on top is not below that, the plan keeps it (SO20
 // at 1180 x 1980: 41 against 32 us per step).
-// The model knows neither the caches nor rounds past its grids: 3700 random
-// grids up to 25 M nodes gave, per radius and precision, the number of nodes
+// The model knows neither the caches nor rounds past its grids: 4200 random
+// grids up to 200 M nodes gave, per radius and precision, the number of nodes
 // above which single steps are the faster ones.  Tiles that are mostly halo
 // (SO18, SO20; SO12 and SO14 in doubles) lose first, the others once the
 // levels of a launch outgrow the caches.  Rate of several steps over that of
-// single ones: SO20 1.05 at 1.52 M nodes and 0.93 at 1.94 M; in doubles SO6
+// single ones: SO20 1.05 at 1.52 M nodes and 0.93 at 1.94 M, SO10 1.14 at
+// 20.8 M and 0.91 at 28.8 M, SO12 1.09 at 21.7 M and 0.86 at 29.4 M (between 34
+// and 82 M some grids gain up to 1.2 again, as many lose); in doubles SO6
 // 1.09 at 13.1 M and 0.95 at 18.6 M, SO8 1.14 at 11.9 M and 0.96 at 16.7 M,
 // SO10 1.07 at 9.7 M and 0.87 at 12.5 M, SO12 1.08 at 1.0 M and 0.88 at
-// 1.24 M, SO14 1.13 at 0.27 M and 0.88 at 0.41 M.  Of 2700 grids
-// that still take several steps one is more than 1% slower than with single
-// steps (SO12, 23.5 M: 0.988).
+// 1.24 M, SO14 1.13 at 0.27 M and 0.88 at 0.41 M.  Of 3000 grids
+// that still take several steps none is more than 1% slower than with single
+// steps.
 Multi2DChoice choose_multi2d(int r, int value_bytes, int Z, int Y, int cus)
 {
     Multi2DChoice best{};
     constexpr double kNone = 1e18;
-    constexpr double kNodes32[11] = {0, kNone, kNone, kNone, kNone, kNone, kNone, kNone, kNone, 1.45e6, 1.45e6};
+    constexpr double kNodes32[11] = {0, kNone, kNone, kNone, kNone, 23e6, 23e6, kNone, kNone, 1.45e6, 1.45e6};
     constexpr double kNodes64[11] = {0, kNone, kNone, 15.5e6, 14e6, 10e6, 1.1e6, 0.3e6, kNone, kNone, kNone};
     if (double(Z) * Y > (value_bytes == 4 ? kNodes32 : kNodes64)[r]) return best;
     double cost = (8.5 + 1.75 * r + 1e-6 * value_bytes * double(Z) * Y) / 1.25;

@@ -134,6 +134,10 @@ def test_threads_share_a_plan():
     ((750, 1030), 12, "float64", "steps"),
     ((720, 710), 14, "float64", "block"),
     ((500, 500), 14, "float64", "steps"),
+    ((11560, 2510), 10, "float32", "block"),
+    ((7460, 2600), 10, "float32", "steps"),
+    ((1940, 15280), 12, "float32", "block"),
+    ((4500, 3570), 12, "float32", "steps"),
     ((979, 1954), 20, "float32", "block"),
     ((900, 900), 20, "float32", "steps"),
 ])
